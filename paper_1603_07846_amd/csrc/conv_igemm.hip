@@ -16,7 +16,10 @@
 // the LDS rows.  The t range is split across workgroups (split-K); partial
 // sums go to a buffer that a second kernel reduces in a fixed order.
 //
-// Tiling: 256 threads (4 wave64) per workgroup, a 128 x 128 output tile,
+// Forward GEMMs of whole 16-byte tap vectors run on the tiles of
+// conv_fwd_tile.hip or, bf16 with many rows, on the 256-row kernel below; the
+// rest (and the dense backward-data that reads the weights transposed):
+// 256 threads (4 wave64) per workgroup, a 128 x 128 output tile,
 // each wave a 64 x 64 quadrant made of 2 x 2 blocks of 32 x 32 MFMA
 // (v_mfma_f32_32x32x2_f32 for fp32, v_mfma_f32_32x32x16_bf16 for bf16).
 // A K-tile is 128 bytes of every operand row (32 fp32 or 64 bf16 taps); LDS
@@ -24,16 +27,13 @@
 // consecutive rows hit distinct banks.  Two LDS stages: global loads of tile
 // k+1 are in flight while tile k is multiplied.
 #include <algorithm>
-#include <cstdlib>
 
-#include "common.h"
-#include "internal.h"
+#include "conv_common.h"
 
 namespace singa {
 
 namespace {
 
-constexpr int NT = 256;
 constexpr int BM = 128;
 constexpr int BN = 128;
 constexpr int ROWB = 128;               // bytes of one operand row per K-tile
@@ -49,39 +49,6 @@ template <typename T> struct KT {
   static constexpr int BK = ROWB / (int)sizeof(T); // taps per K-tile
 };
 
-union V16 {
-  uint4 u;
-  float f[4];
-  bf16_t h[8];
-};
-
-template <typename T> __device__ __forceinline__ void set_elem(V16& v, int j, T e);
-template <> __device__ __forceinline__ void set_elem<float>(V16& v, int j, float e) { v.f[j] = e; }
-template <> __device__ __forceinline__ void set_elem<bf16_t>(V16& v, int j, bf16_t e) { v.h[j] = e; }
-
-template <typename T> __device__ __forceinline__ T one_elem();
-template <> __device__ __forceinline__ float one_elem<float>() { return 1.f; }
-template <> __device__ __forceinline__ bf16_t one_elem<bf16_t>() { return (bf16_t)0x3f80; }
-
-template <typename T> __device__ __forceinline__ T zero_elem();
-template <> __device__ __forceinline__ float zero_elem<float>() { return 0.f; }
-template <> __device__ __forceinline__ bf16_t zero_elem<bf16_t>() { return (bf16_t)0; }
-
-template <typename T> __device__ __forceinline__ void store_out(T* p, float v);
-template <> __device__ __forceinline__ void store_out<float>(float* p, float v) { *p = v; }
-template <> __device__ __forceinline__ void store_out<bf16_t>(bf16_t* p, float v) { *p = f32_to_bf16(v); }
-
-__device__ __forceinline__ float elem_f(float v) { return v; }
-__device__ __forceinline__ float elem_f(bf16_t v) { return bf16_to_f32(v); }
-
-// ReLU backward folded into an epilogue: keep v where the ReLU's output is > 0.
-template <typename T> __device__ __forceinline__ bool mask_pass(const void* m, size_t i);
-template <> __device__ __forceinline__ bool mask_pass<float>(const void* m, size_t i) {
-  return ((const float*)m)[i] > 0.f;
-}
-template <> __device__ __forceinline__ bool mask_pass<bf16_t>(const void* m, size_t i) {
-  return bf16_to_f32(((const bf16_t*)m)[i]) > 0.f;
-}
 
 // Multiply one K-tile held in LDS: acc[bm][bn] += A(rows) * B(cols)^T.
 template <typename T>
@@ -154,210 +121,6 @@ __device__ __forceinline__ void mma_tile_bt(const char* As, const char* Bs, f32x
   }
 }
 
-// ------------------------------------------------------------ global loads
-//
-// Operands are read with raw buffer loads: a tap outside the input (padding,
-// ragged tails) gets the offset OOB, past the end of every tensor, and the
-// hardware returns zeros for it.  No branch, no select on the loaded data.
-constexpr uint32_t OOB = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ uint4 ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-__device__ __forceinline__ uint2 ld8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-template <typename T> __device__ __forceinline__ T ld_elem(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <> __device__ __forceinline__ float ld_elem<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
-template <> __device__ __forceinline__ bf16_t ld_elem<bf16_t>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return (bf16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
-}
-
-// Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous
-// run of tiles so neighbouring tiles (shared input rows, shared filters) meet
-// in the same L2.
-__device__ __forceinline__ int xcd_remap(int b, int G) {
-  const int q = G >> 3, r = G & 7, x = b & 7, l = b >> 3;
-  return x * q + min(x, r) + l;
-}
-
-// All-ones in the bits of each element of a 32-bit word that is > 0 (not
-// NaN), zero elsewhere, from the bit patterns alone: with x = bits - 1 taken
-// as a signed integer, an element is > 0 exactly when 0 <= x < bits(+inf).
-// Integer arithmetic only, so a mask of many elements needs no condition
-// registers.
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-template <typename T> __device__ __forceinline__ uint32_t positive_bits(uint32_t w);
-template <> __device__ __forceinline__ uint32_t positive_bits<bf16_t>(uint32_t w) {
-  const int32_t xl = (int32_t)(w & 0xffffu) - 1, xh = (int32_t)(w >> 16) - 1;
-  const uint32_t ml = (uint32_t)(((xl - 0x7f80) >> 31) & ~(xl >> 31)) & 0xffffu;
-  const uint32_t mh = (uint32_t)(((xh - 0x7f80) >> 31) & ~(xh >> 31)) << 16;
-  return ml | mh;
-}
-template <> __device__ __forceinline__ uint32_t positive_bits<float>(uint32_t w) {
-  const uint32_t x = w - 1u;
-  return (uint32_t)(((int32_t)(x - 0x7f800000u) >> 31) & ~((int32_t)x >> 31));
-}
-
-// ------------------------------------------------------------ epilogue
-//
-// y[row][col] = act(acc + bias[col]), optionally zeroed where mask <= 0, for
-// row blocks B0 .. B0 + NB - 1 of one wave's (32 FM) x (32 FN) quadrant of
-// the output tile (row0: the first row of block B0).  The accumulators hold
-// one column per lane (rows 8 (v / 4) + 4 (lane / 32) + v % 4 of each 32 x 32
-// block); they go through the wave's own LDS region as T so that the global
-// stores (and the mask loads) are 16-byte vectors of consecutive columns.
-// Needs (32 NB) * (32 FN * sizeof(T) + 16) bytes of LDS at `lds`; the caller
-// has finished with the operand tiles there (barrier).  `vec`: y, mask and Nn
-// allow 16-byte vectors; otherwise the staged values are stored one by one.
-template <typename T, int FM, int FN, int B0 = 0, int NB = FM>
-__device__ __forceinline__ void store_quadrant(const f32x16 (&acc)[FM][FN], char* lds, int lane, int row0, int col0,
-                                               int M, int Nn, const float* bias, int relu, const void* mask,
-                                               T* __restrict__ y, bool vec) {
-  constexpr int ES = (int)sizeof(T);
-  constexpr int COLS = FN * 32;
-  constexpr int PIT = COLS * ES + 16;
-  constexpr int VEC = 16 / ES;
-  constexpr int CPR = COLS / VEC;    // 16-byte chunks per row
-  constexpr int RPS = 64 / CPR;      // rows per pass of the wave (lanes past RPS * CPR idle)
-  constexpr int PASSES = (NB * 32 + RPS - 1) / RPS;
-  const int li = lane & 31, lh = lane >> 5;
-  const int cc = lane % CPR, rr = lane / CPR;
-  const int col = col0 + cc * VEC;
-  const T* __restrict__ mk = (const T*)mask;
-  // The mask vectors of every pass are requested before the values are
-  // staged, so their latency overlaps the staging and each other (one load
-  // waited for per pass would expose a memory latency per pass).
-  uint4 mv[PASSES];
-  if (vec && mk) {
-#pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-      const int r = pass * RPS + rr;
-      const int row = row0 + r;
-      // every lane loads (element 0 stands in for rows and columns past the
-      // end), so no load sits in a branch that the next must wait for
-      const bool ok = rr < RPS && r < NB * 32 && row < M && col < Nn;
-      mv[pass] = *(const uint4*)(mk + (ok ? (size_t)row * Nn + col : 0));
-    }
-  }
-#pragma unroll
-  for (int bn = 0; bn < FN; ++bn) {
-    const int c = bn * 32 + li;
-    const float bv = (bias && col0 + c < Nn) ? bias[col0 + c] : 0.f;
-#pragma unroll
-    for (int bm = B0; bm < B0 + NB; ++bm)
-#pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        // rows r and r + 1 of column c
-        float v0 = acc[bm][bn][v] + bv, v1 = acc[bm][bn][v + 1] + bv;
-        if (relu) {
-          v0 = fmaxf(v0, 0.f);
-          v1 = fmaxf(v1, 0.f);
-        }
-        const int r = (bm - B0) * 32 + (v >> 2) * 8 + lh * 4 + (v & 3);
-        if constexpr (sizeof(T) == 2) {
-          // one conversion instruction rounds both (the per-element
-          // software rounding costs about six VALU operations per value)
-          const uint32_t p = f32x2_to_bf16x2(v0, v1);
-          *(uint16_t*)(lds + r * PIT + c * ES) = (uint16_t)p;
-          *(uint16_t*)(lds + (r + 1) * PIT + c * ES) = (uint16_t)(p >> 16);
-        } else {
-          store_out<T>((T*)(lds + r * PIT + c * ES), v0);
-          store_out<T>((T*)(lds + (r + 1) * PIT + c * ES), v1);
-        }
-      }
-  }
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
-  __builtin_amdgcn_wave_barrier();
-  if (rr >= RPS) return;
-  if (vec) {
-#pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-      const int r = pass * RPS + rr;
-      const int row = row0 + r;
-      if (r >= NB * 32) break;
-      uint4 val = *(const uint4*)(lds + r * PIT + cc * 16);
-      if (row < M && col < Nn) {
-        if (mk) {
-          val.x &= positive_bits<T>(mv[pass].x);
-          val.y &= positive_bits<T>(mv[pass].y);
-          val.z &= positive_bits<T>(mv[pass].z);
-          val.w &= positive_bits<T>(mv[pass].w);
-        }
-        // streamed past the caches' write allocation (measured 0.5-3 % faster
-        // per layer, the consumers included)
-        __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, val), (u32x4_t*)(y + (size_t)row * Nn + col));
-      }
-    }
-  } else {
-#pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-      const int r = pass * RPS + rr;
-      const int row = row0 + r;
-      if (r >= NB * 32) break;
-      union { uint4 u; T e[VEC]; } val;
-      val.u = *(const uint4*)(lds + r * PIT + cc * 16);
-      if (row < M) {
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-          const int cj = col + j;
-          if (cj < Nn) {
-            const size_t o = (size_t)row * Nn + cj;
-            T e = val.e[j];
-            if (mk && !(elem_f(mk[o]) > 0.f)) e = T(0);
-            y[o] = e;
-          }
-        }
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------------ forward
-
-struct FwdArgs {
-  const void* x;
-  const void* w;
-  const float* bias;
-  void* y;
-  uint32_t x_bytes, w_bytes;
-  int M, Nn, Kg;
-  int H, W, C, S, P, Q;
-  int sh, sw, ph, pw;
-  FastDiv dPQ, dQ, dC, dS;
-  int relu;
-  int tiles, tiles_n;
-  float* partial;  // split-K: fp32 partial tiles [split][M][Nn] instead of y
-  int kt_per_split;
-  const void* mask;  // optional [M][Nn] tensor: an output is zeroed where mask <= 0
-  // 256-row kernel: K-tile kt covers channels [cs BK, cs BK + BK) of tap
-  // rs = kt mod RS, cs = kt div RS (taps fastest), instead of taps [kt BK,
-  // kt BK + BK) in (r, s, c) order; needs C % BK == 0.
-  int tap_major, RS;
-  FastDiv dRS;
-  // input patch (stride 1, tap-major): the padded input is Hp x Wp per image
-  int patch, Hp, Wp;
-  FastDiv dHp, dWp;
-};
-
-// Operand load modes.  VEC16: 16-byte vectors of VEC taps (C % VEC == 0 for
-// the input, Kg % VEC == 0 for the filter rows).  VEC8 (bf16 only): two 8-byte
-// halves of 4 taps each, for channel counts that are a multiple of 4 but not
-// of 8 (the first layer's colour channels padded to 4).  ELEM: one element at
-// a time.
-// BT16 (bf16 filter only): the filter is given transposed, w[tap][col] with
-// the Nn columns contiguous (Nn % 8 == 0); 16-byte vectors of 8 columns go
-// into LDS as tap-major rows and the MFMA fragments come from transposing
-// reads.  Serves the dense backward-data, whose B operand is the weight
-// matrix as stored, without a transposed copy.
-constexpr int ELEM = 0, VEC8 = 1, VEC16 = 2, BT16 = 3;
 
 
 // AM / BMD: load mode of the input taps / filter rows.  BWD only names the
@@ -597,34 +360,6 @@ template <int LBK> struct LT {
   static constexpr int KS = LBK / 16;                 // MFMA k-steps per K-tile
 };
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-// One 16-byte buffer load per lane into LDS slot (base + 16 * lane); base is
-// wave-uniform.
-__device__ __forceinline__ void ld_lds16(__amdgpu_buffer_rsrc_t r, uint32_t off, char* base) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)base, 16, off, 0, 0, 0);
-}
-
-// The same load issued from inline assembly.  The compiler then does not
-// know that the instruction writes LDS, so it adds no vmcnt wait in front of
-// later LDS reads (it does so for the transpose reads, which would serialize
-// every prefetch); the kernel orders the two itself with wait_vmcnt and a
-// barrier.  M0 carries the LDS address; no other code of these kernels uses
-// M0.
-__device__ __forceinline__ void ld_lds16_asm(__amdgpu_buffer_rsrc_t r, uint32_t off, char* base) {
-  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)base;
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds)),
-               "v"(off), "s"(r)
-               : "memory");
-}
-
-// s_waitcnt vmcnt(n) (n < 64), leaving the other counters alone.
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-__device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // WMW = 2: waves 2 (rows) x 2 (columns), each 128 x 64 of a 256 x 128 tile.
 // WMW = 4: waves stacked along the rows, each 64 x 96 of a 256 x 96 tile, for
@@ -1807,17 +1542,6 @@ __global__ __launch_bounds__(256) void splitk_epilogue_vec_kernel(const float* _
   }
 }
 
-// Layout and split overrides for A/B measurements (SINGA_CONV_TILE,
-// SINGA_FWD_BK, SINGA_FWD_WIDE, SINGA_FWD_SHORT, SINGA_FWD_PATCH, SINGA_WGRAD_ORDER, SINGA_WGRAD_TARGET): read
-// from the environment only in a library built with -DSINGA_TUNING.  The
-// default build ignores the environment; its dispatch rules are the tested
-// ones.
-#ifdef SINGA_TUNING
-inline const char* tuning_env(const char* name) { return getenv(name); }
-#else
-constexpr const char* tuning_env(const char*) { return nullptr; }
-#endif
-
 // "conv_fwd_kernel<dtype,modeA,modeB,bwd>" for each instance, as string
 // literals (the launch path writes no state)
 #define FWD_NAME(T, A, B, W) "conv_fwd_kernel<" T "," #A "," #B "," #W ">"
@@ -1963,7 +1687,7 @@ int fwd_splits_for(long M, long Nn, long Kg, long bk) {
 template <typename T, int AM, bool BWD>
 void launch_fwd_bmode(int bm, const FwdArgs& a, dim3 grid, double flops, hipStream_t st) {
   if (sizeof(T) == 2 && bm == BT16) launch_fwd_instance<T, AM, sizeof(T) == 2 ? BT16 : ELEM, BWD>(a, grid, flops, st);
-  else if (bm == VEC16) launch_fwd_instance<T, AM, VEC16, BWD>(a, grid, flops, st);
+  else if (bm == VEC16) launch_fwd_instance<T, AM == VEC16 ? ELEM : AM, VEC16, BWD>(a, grid, flops, st);  // both VEC16: the tile kernel
   else if (sizeof(T) == 2 && bm == VEC8) launch_fwd_instance<T, AM, sizeof(T) == 2 ? VEC8 : ELEM, BWD>(a, grid, flops, st);
   else launch_fwd_instance<T, AM, ELEM, BWD>(a, grid, flops, st);
 }
@@ -2012,13 +1736,18 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
   a.tiles = tiles_m * a.tiles_n;
   constexpr int BK = KT<T>::BK;
   const int nkt = (a.Kg + BK - 1) / BK;
-  const int splits = partial ? fwd_splits_for(a.M, a.Nn, a.Kg, BK) : 1;
+  const int am = load_mode<T>(s.C, x);
+  const int bm = wt ? BT16 : load_mode<T>(a.Kg, w);
+  const bool vec16 = am == VEC16 && bm == VEC16;
+  const bool large = vec16 && sizeof(T) == 2 && use_large_fwd(a.M, a.Nn, a.Kg) && !tuning_env("SINGA_FWD_TILE");
+  const int segs = fwd_splits_for(a.M, a.Nn, a.Kg, BK);
+  const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, sizeof(T) == 2 ? BF16 : F32, segs)
+                                           : FwdTilePlan{0, 1, 1};
+  const int splits = vec16 ? plan.splits : segs;
   a.partial = splits > 1 ? partial : nullptr;
   a.kt_per_split = (nkt + splits - 1) / splits;
   dim3 grid(a.tiles * splits);
-  const int am = load_mode<T>(s.C, x);
-  const int bm = wt ? BT16 : load_mode<T>(a.Kg, w);
-  if (!wt && sizeof(T) == 2 && am == VEC16 && bm == VEC16 && splits == 1 && use_large_fwd(a.M, a.Nn, a.Kg)) {
+  if (large) {
     const bool narrow = a.Nn <= 96;  // one 96-column tile
     const bool wide = use_wide_fwd(a.M, a.Nn);
     const bool short_wide = wide && use_short_wide_fwd(a.M, a.Nn);
@@ -2063,11 +1792,16 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
 #undef LAUNCH_PATCH
     return hipGetLastError();
   }
-  if (bwd)
-    launch_fwd_variant<T, true>(am, bm, a, grid, flops, st);
-  else
-    launch_fwd_variant<T, false>(am, bm, a, grid, flops, st);
-  hipError_t e = hipGetLastError();
+  hipError_t e;
+  if (vec16) {
+    e = launch_conv_fwd_tile(sizeof(T) == 2 ? BF16 : F32, a, plan, bwd, flops, st);
+  } else {
+    if (bwd)
+      launch_fwd_variant<T, true>(am, bm, a, grid, flops, st);
+    else
+      launch_fwd_variant<T, false>(am, bm, a, grid, flops, st);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess || splits == 1) return e;
   const size_t n = (size_t)a.M * a.Nn;
   size_t blocks = (n + 255) / 256;
@@ -2293,7 +2027,9 @@ hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const v
 
 size_t fwd_partial_bytes(const ConvShape& s, int dt) {
   const long M = (long)s.N * s.P * s.Q, Nn = s.K, Kg = (long)s.R * s.S * s.C;
-  const int splits = fwd_splits_for(M, Nn, Kg, dt == BF16 ? KT<bf16_t>::BK : KT<float>::BK);
+  // either kernel may run (the tile kernel also needs aligned pointers)
+  const int segs = fwd_splits_for(M, Nn, Kg, dt == BF16 ? KT<bf16_t>::BK : KT<float>::BK);
+  const int splits = dt == BF16 ? segs : std::max(segs, fwd_tile_plan(M, Nn, Kg, dt, segs).splits);
   return splits > 1 ? (size_t)splits * M * Nn * sizeof(float) : 0;
 }
 

@@ -1,0 +1,111 @@
+"""Every tile of the direct-to-LDS forward kernel against the oracle.
+
+Each case is small but takes one tile (checked through the kernel trace) in
+one way of summing the taps: in one piece ("one"), in several pieces that a
+workgroup adds in order ("seg", bf16), or in one piece per workgroup with a
+reduction after it ("split").  Rows, columns and taps are ragged; channel
+counts are multiples of a K-tile, of a vector only, or in between.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1603_07846_amd import singa
+from paper_1603_07846_amd import workloads as wl
+from _helpers import TOL, dev_to_nchw, kcrs_to_dev, nchw_to_dev, phys, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # dtype, tile, summation, (N, C, H, W, K, R, S, pad, stride)
+    ("bf16", "128x128", "one", (48, 16, 30, 25, 77, 1, 1, 0, 1)),
+    ("bf16", "128x128", "split", (8, 168, 18, 20, 137, 5, 5, 2, 1)),
+    ("bf16", "128x32", "one", (16, 16, 26, 26, 93, 1, 1, 0, 1)),
+    ("bf16", "128x32", "seg", (48, 56, 4, 23, 198, 3, 3, 1, 1)),
+    ("bf16", "128x32", "split", (3, 352, 35, 10, 8, 5, 5, 2, 1)),
+    ("bf16", "128x64", "one", (31, 8, 30, 21, 161, 1, 1, 0, 1)),
+    ("bf16", "128x64", "split", (48, 208, 7, 17, 33, 3, 3, 1, 1)),
+    ("bf16", "192x128", "one", (64, 32, 40, 14, 76, 5, 5, 2, 1)),
+    ("bf16", "192x128", "split", (2, 216, 30, 37, 68, 5, 5, 2, 1)),
+    ("bf16", "256x128", "one", (64, 24, 15, 27, 148, 5, 5, 2, 1)),
+    ("bf16", "256x128", "split", (31, 280, 28, 3, 135, 3, 3, 1, 1)),
+    ("bf16", "256x64", "one", (64, 8, 31, 37, 44, 1, 1, 0, 1)),
+    ("bf16", "256x64", "split", (64, 328, 4, 27, 36, 3, 3, 1, 1)),
+    ("bf16", "32x128", "seg", (2, 200, 34, 40, 384, 3, 3, 1, 1)),
+    ("bf16", "32x128", "split", (2, 144, 21, 16, 106, 5, 5, 2, 1)),
+    ("bf16", "64x128", "one", (31, 8, 37, 26, 97, 1, 1, 0, 1)),
+    ("bf16", "64x128", "seg", (24, 64, 25, 20, 168, 3, 3, 1, 1)),
+    ("bf16", "64x128", "split", (12, 80, 9, 13, 163, 5, 5, 2, 1)),
+    ("bf16", "64x64", "one", (2, 8, 7, 4, 57, 1, 1, 0, 1)),
+    ("bf16", "64x64", "seg", (3, 56, 6, 4, 13, 3, 3, 1, 1)),
+    ("bf16", "64x64", "split", (1, 80, 10, 12, 19, 3, 3, 1, 1)),
+    ("f32", "128x128", "one", (8, 4, 25, 30, 355, 1, 1, 0, 1)),
+    ("f32", "128x128", "split", (12, 180, 36, 39, 106, 3, 3, 1, 1)),
+    ("f32", "128x32", "one", (24, 36, 36, 21, 9, 1, 1, 0, 1)),
+    ("f32", "128x32", "split", (5, 144, 39, 12, 8, 3, 3, 1, 1)),
+    ("f32", "128x64", "one", (24, 4, 31, 28, 35, 3, 3, 1, 1)),
+    ("f32", "128x64", "split", (3, 152, 36, 26, 38, 3, 3, 1, 1)),
+    ("f32", "192x128", "one", (48, 28, 40, 8, 309, 3, 3, 1, 1)),
+    ("f32", "192x128", "split", (24, 36, 36, 13, 78, 5, 5, 2, 1)),
+    ("f32", "256x128", "one", (48, 32, 34, 12, 366, 3, 3, 1, 1)),
+    ("f32", "256x128", "split", (64, 80, 15, 19, 101, 3, 3, 1, 1)),
+    ("f32", "256x64", "one", (31, 8, 32, 36, 48, 1, 1, 0, 1)),
+    ("f32", "256x64", "split", (12, 80, 38, 31, 142, 3, 3, 1, 1)),
+    ("f32", "32x128", "one", (3, 156, 25, 36, 356, 1, 1, 0, 1)),
+    ("f32", "32x128", "split", (2, 184, 5, 27, 199, 3, 3, 1, 1)),
+    ("f32", "64x128", "one", (8, 4, 34, 29, 158, 1, 1, 0, 1)),
+    ("f32", "64x128", "split", (12, 120, 5, 22, 66, 5, 5, 2, 1)),
+    ("f32", "64x64", "one", (3, 8, 7, 4, 40, 1, 1, 0, 1)),
+    ("f32", "64x64", "split", (1, 176, 6, 12, 21, 1, 1, 0, 1)),
+]
+
+
+def _data(case, dt, seed):
+    N, C, H, W, K, R, S, pad, stride = case
+    x = wl.random_array((N, C, H, W), seed, "normal", 1.0, dt)
+    w = wl.random_array((K, C, R, S), seed + 1, "normal", 0.1, dt)
+    b = wl.random_array((K,), seed + 2, "normal", 0.5, "f32")
+    return x, w, b
+
+
+@pytest.mark.parametrize("dt,tile,how,case", CASES,
+                         ids=["-".join(c[:3]) + "-" + "x".join(map(str, c[3])) for c in CASES])
+def test_forward_tile(dt, tile, how, case):
+    N, C, H, W, K, R, S, pad, stride = case
+    x, w, b = _data(case, dt, 300)
+    singa.trace_enable(True)
+    y = singa.conv_fwd(nchw_to_dev(x, dt), kcrs_to_dev(w, dt), torch.from_numpy(b).cuda(), pad, stride, relu=True)
+    torch.cuda.synchronize()
+    names = [r[0] for r in singa.trace_records()]
+    singa.trace_enable(False)
+    assert "conv_fwd_kernel<%s,%s,0>" % (dt, tile) in names, names
+    assert ("splitk_epilogue_kernel" in names) == (how == "split"), names
+    ref = oracle.relu_fwd(oracle.conv_fwd(x, w, b, pad=pad, stride=stride))
+    assert rel_l2(dev_to_nchw(y), ref) <= TOL[dt]
+
+
+# the source gradient: the same kernel with a folded ReLU mask, at stride 1
+# and 2 (the latter on the space-to-depth layer)
+BWD_CASES = [(3, 40, 14, 11, 72, 3, 3, 1, 1), (2, 64, 13, 13, 128, 5, 5, 2, 1), (6, 96, 9, 9, 200, 1, 1, 0, 1),
+             (3, 24, 15, 13, 64, 3, 3, 1, 2)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", BWD_CASES, ids=["x".join(map(str, c)) for c in BWD_CASES])
+def test_source_gradient_tile(case, dt):
+    N, C, H, W, K, R, S, pad, stride = case
+    x, w, _ = _data(case, dt, 310)
+    xr = np.maximum(x, 0.0)
+    P, Q = oracle.conv_out(H, R, pad, stride), oracle.conv_out(W, S, pad, stride)
+    dy = wl.random_array((N, K, P, Q), 313, "normal", 1.0, dt)
+    singa.trace_enable(True)
+    dx = singa.conv_bwd_data(nchw_to_dev(dy, dt), kcrs_to_dev(w, dt), phys(x.shape), pad, stride,
+                             relu_y=nchw_to_dev(xr, dt))
+    torch.cuda.synchronize()
+    names = [r[0] for r in singa.trace_records()]
+    singa.trace_enable(False)
+    assert any(n.startswith("conv_fwd_kernel<%s," % dt) and "x" in n.split(",")[1] for n in names), names
+    ref = oracle.relu_bwd(xr, oracle.conv_bwd_data(dy, w, x.shape, pad=pad, stride=stride))
+    got = dev_to_nchw(dx)
+    np.testing.assert_array_equal(got[xr <= 0], 0.0)
+    assert rel_l2(got, ref) <= TOL[dt]
