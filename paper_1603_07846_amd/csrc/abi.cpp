@@ -163,7 +163,7 @@ bool s2d_input_ok(const ConvShape& s, int dt) {
 // the two can never disagree.
 struct FwdWs { void *x, *w, *y, *xp, *wp; float* partial; };
 struct BwdDataWs { void *dy, *w, *wt, *dx, *ws, *dxs; float* partial; };
-struct BwdFilterWs { void *x, *dy, *xp; float *dw, *dwp, *partial; };
+struct BwdFilterWs { void *x, *dy, *xp; float *dw, *dwp, *partial; size_t partial_bytes; };
 
 size_t carve_fwd(const ConvShape& s, int dt, int layout, void* ws, FwdWs* o) {
   Carve c(ws);
@@ -229,7 +229,8 @@ size_t carve_bwd_data(const ConvShape& s, int dt, int layout, void* ws, BwdDataW
   return c.used;
 }
 
-size_t carve_bwd_filter(const ConvShape& s, int dt, int layout, bool bias, void* ws, BwdFilterWs* o) {
+size_t carve_bwd_filter(const ConvShape& s, int dt, int layout, bool bias, void* ws, BwdFilterWs* o,
+                        bool least = false) {
   Carve c(ws);
   o->x = o->dy = o->xp = nullptr;
   o->dw = o->dwp = nullptr;
@@ -243,8 +244,8 @@ size_t carve_bwd_filter(const ConvShape& s, int dt, int layout, bool bias, void*
     if (layout != SINGA_NHWC_S2D) o->xp = c.take((size_t)g.N * g.H * g.W * g.C * dt_size(dt));
     o->dwp = (float*)c.take((size_t)g.K * g.R * g.S * g.C * sizeof(float));
   }
-  const size_t pb = wgrad_partial_bytes(g, dt, bias);
-  o->partial = pb ? (float*)c.take(pb) : nullptr;
+  o->partial_bytes = wgrad_partial_bytes(g, dt, bias, least);
+  o->partial = o->partial_bytes ? (float*)c.take(o->partial_bytes) : nullptr;
   return c.used;
 }
 
@@ -500,9 +501,13 @@ int singa_conv_bwd_filter(singa_dtype dtype, singa_layout layout, const singa_sh
     return SINGA_ERR_ALIGN;
   BwdFilterWs o;
   const bool bias = db != nullptr;
-  const size_t need = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o);
+  // a workspace that holds only the least number of partial tiles (the fixed
+  // scratch array's limit) still serves, with fewer splits
+  size_t need = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o);
+  const bool least = ws_bytes < need;
+  if (least) need = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o, true);
   if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
-  carve_bwd_filter(s, dtype, layout, bias, ws, &o);
+  carve_bwd_filter(s, dtype, layout, bias, ws, &o, least);
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const void* xx = x_ptr;
@@ -525,7 +530,7 @@ int singa_conv_bwd_filter(singa_dtype dtype, singa_layout layout, const singa_sh
   const int tacc = rw != RW_NONE ? 0 : acc;
   // db is written in place by the GEMM's bias column, with the caller's accumulate
   if (e == hipSuccess)
-    e = launch_conv_wgrad(dtype, g, xx, dy, o.partial, target, db, tacc, accumulate, conv_flops(s), st);
+    e = launch_conv_wgrad(dtype, g, xx, dy, o.partial, o.partial_bytes, target, db, tacc, accumulate, conv_flops(s), st);
   if (e == hipSuccess && rw == RW_PAD)
     e = launch_unpad_channels_f32(o.dwp, krsc, (long)s.K * s.R * s.S, g.C, s.C, acc, st);
   if (e == hipSuccess && rw == RW_S2D) e = launch_s2d_to_filter_f32(s, g, o.dwp, krsc, acc, st);

@@ -250,6 +250,36 @@ struct FwdArgs {
   FastDiv dHp, dWp;
 };
 
+// Arguments of the filter-gradient kernels.  With a bias, the GEMM gets one more column, Ng = Nn + 1, whose operand is
+// 1 for every reduction index: its results are db[k] = sum_t dy[t][k].
+struct WgradArgs {
+  const void* x;
+  const void* dy;
+  float* out;  // partial tiles [splits][M][Ng], or dw itself when direct
+  float* db;   // direct: the bias gradient (column Nn); NULL without bias
+  uint32_t x_bytes, dy_bytes;
+  int M, Nn, Ng, T;  // M = K filters, Nn = R*S*C taps, Ng = Nn (+1 with bias), T = N*P*Q
+  int ldp;           // row stride of the partial tiles: Ng rounded up to 64 (256-byte rows)
+  int N, H, W, C, S, P, Q;
+  int sh, sw, ph, pw;
+  FastDiv dN, dPQ, dQ, dC, dS;
+  int tiles, tiles_n, kt_per_split, nkt;
+  int direct, acc_dw, acc_db;
+  int update;    // direct only: each element is applied to `u` (out / db: NULL, or where g is also stored)
+  SgdTargets u;
+};
+
+// Tile and reduction splits of the fp32 tile kernel (conv_wgrad_tile.hip).
+struct WgradTilePlan {
+  int tile;    // index into the kernel's table of tiles
+  int splits;  // > 1: partial tiles in WgradArgs::out
+  bool nfast;  // a K-tile is 32 images at one output pixel
+};
+// max_splits: what the caller's workspace has room for.
+WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits);
+int wgrad_tile_rows(int tile);
+hipError_t launch_conv_wgrad_tile(WgradArgs a, const WgradTilePlan& p, double flops, hipStream_t st);
+
 // Tile and tap splits of the direct-to-LDS tile kernel (conv_fwd_tile.hip)
 // for a GEMM of M rows, Nn columns and Kg taps, whose operands are whole
 // 16-byte vectors.

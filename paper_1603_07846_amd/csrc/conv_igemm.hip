@@ -27,6 +27,7 @@
 // consecutive rows hit distinct banks.  Two LDS stages: global loads of tile
 // k+1 are in flight while tile k is multiplied.
 #include <algorithm>
+#include <climits>
 
 #include "conv_common.h"
 
@@ -738,24 +739,6 @@ template <> struct WG<float> {
 };
 constexpr int WSMEM = 2 * 2 * 64 * 320;  // 2 stages x 2 operands (equal for both dtypes)
 
-// With a bias, the GEMM gets one more column, Ng = Nn + 1, whose operand is
-// 1 for every reduction index: its results are db[k] = sum_t dy[t][k].
-struct WgradArgs {
-  const void* x;
-  const void* dy;
-  float* out;  // partial tiles [splits][M][Ng], or dw itself when direct
-  float* db;   // direct: the bias gradient (column Nn); NULL without bias
-  uint32_t x_bytes, dy_bytes;
-  int M, Nn, Ng, T;  // M = K filters, Nn = R*S*C taps, Ng = Nn (+1 with bias), T = N*P*Q
-  int ldp;           // row stride of the partial tiles: Ng rounded up to 64 (256-byte rows)
-  int N, H, W, C, S, P, Q;
-  int sh, sw, ph, pw;
-  FastDiv dN, dPQ, dQ, dC, dS;
-  int tiles, tiles_n, kt_per_split, nkt;
-  int direct, acc_dw, acc_db;
-  int update;    // direct only: each element is applied to `u` (out / db: NULL, or where g is also stored)
-  SgdTargets u;
-};
 
 
 // One K-tile of t-major operand rows: acc[bm][bn] += A(rows) * B(cols)^T.
@@ -1843,7 +1826,8 @@ void launch_wgrad_instance(const WgradArgs& a, dim3 grid, double flops, hipStrea
 
 template <typename T, bool VA, bool NF>
 void launch_wgrad_bmode(int bm, const WgradArgs& a, dim3 grid, double flops, hipStream_t st) {
-  if (bm == VEC16) launch_wgrad_instance<T, VA, VEC16, NF>(a, grid, flops, st);
+  // fp32 with vectors of both operands: the tile kernel
+  if (bm == VEC16) launch_wgrad_instance<T, VA, sizeof(T) == 4 && VA ? ELEM : VEC16, NF>(a, grid, flops, st);
   else if (sizeof(T) == 2 && bm == VEC8)
     launch_wgrad_instance<T, VA, sizeof(T) == 2 ? VEC8 : ELEM, NF>(a, grid, flops, st);
   else launch_wgrad_instance<T, VA, ELEM, NF>(a, grid, flops, st);
@@ -1920,7 +1904,8 @@ int wgrad_splits_for(const ConvShape& s, int dt, bool bias, bool large) {
 }
 
 template <typename T>
-hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy, float* partial, float* dw,
+hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy, float* partial,
+                               size_t partial_bytes, float* dw,
                                float* db, int acc_dw, int acc_db, const SgdTargets* upd, double flops,
                                hipStream_t st) {
   constexpr int VEC = 16 / (int)sizeof(T);
@@ -1942,14 +1927,18 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
   const bool va = (a.M % VEC) == 0 && ((uintptr_t)dy % 16) == 0;
   const int vb = load_mode<T>(s.C, x);
   const bool large = wgrad_large_shape(s, DT) && va && vb == VEC16;
-  const int bm = large ? WL_BM : BM, bn = large ? WL_BN : BN, bk = large ? WL_BK : WG<T>::BK;
-  a.nkt = (a.T + bk - 1) / bk;
+  const bool tile = sizeof(T) == 4 && va && vb == VEC16;  // the fp32 tile kernel
   const bool bias = upd ? upd->b != nullptr : db != nullptr;
   a.Ng = a.Nn + (bias ? 1 : 0);
   a.ldp = (a.Ng + 63) / 64 * 64;
+  const long max_splits = (long)(partial_bytes / ((size_t)a.M * a.ldp * sizeof(float)));
+  WgradTilePlan plan = tile ? wgrad_tile_plan(a.M, a.Ng, a.T, max_splits) : WgradTilePlan{0, 1, false};
+  const int bm = large ? WL_BM : tile ? wgrad_tile_rows(plan.tile) : BM, bn = large ? WL_BN : BN;
+  const int bk = large ? WL_BK : WG<T>::BK;
+  a.nkt = (a.T + bk - 1) / bk;
   a.tiles_n = (a.Ng + bn - 1) / bn;
   a.tiles = ((a.M + bm - 1) / bm) * a.tiles_n;
-  const int splits = wgrad_splits_for(s, DT, bias, large);
+  const int splits = tile ? plan.splits : wgrad_splits_for(s, DT, bias, large);
   // the update goes into the large kernel when it writes each element once,
   // otherwise into the split-K reduction; a single split of the 128 x 128
   // kernel has no place for it
@@ -1977,6 +1966,10 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
       if (nf) hipLaunchKernelGGL((conv_wgrad_large_kernel<true, false>), grid, dim3(2 * NT), 0, st, a);
       else hipLaunchKernelGGL((conv_wgrad_large_kernel<false, false>), grid, dim3(2 * NT), 0, st, a);
     }
+  } else if (tile) {
+    plan.nfast = nf;
+    const hipError_t e = launch_conv_wgrad_tile(a, plan, flops, st);
+    if (e != hipSuccess) return e;
   } else if (nf) {
     launch_wgrad_variant<T, true>(va, vb, a, grid, flops, st);
   } else {
@@ -2033,19 +2026,23 @@ size_t fwd_partial_bytes(const ConvShape& s, int dt) {
   return splits > 1 ? (size_t)splits * M * Nn * sizeof(float) : 0;
 }
 
-size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias) {
+size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least) {
   const size_t Ng = (size_t)s.R * s.S * s.C + (bias ? 1 : 0);
   const size_t ldp = (Ng + 63) / 64 * 64;
-  // either kernel may run (the large one also needs aligned pointers)
+  // any of the kernels may run (two of them also need aligned pointers)
   int splits = wgrad_splits_for(s, dt, bias, false);
   if (wgrad_large_shape(s, dt)) splits = std::max(splits, wgrad_splits_for(s, dt, bias, true));
+  if (!least && dt == F32 && s.K % 4 == 0 && s.C % 4 == 0)
+    splits = std::max(splits, wgrad_tile_plan(s.K, (long)Ng, (long)s.N * s.P * s.Q, LONG_MAX).splits);
   return splits > 1 ? (size_t)splits * s.K * ldp * sizeof(float) : 0;
 }
 
-hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial, float* dw,
-                             float* db, int acc_dw, int acc_db, double flops, hipStream_t st) {
-  if (dt == BF16) return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, dw, db, acc_dw, acc_db, nullptr, flops, st);
-  return conv_wgrad_dispatch<float>(s, x, dy, partial, dw, db, acc_dw, acc_db, nullptr, flops, st);
+hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
+                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, double flops,
+                             hipStream_t st) {
+  if (dt == BF16)
+    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, flops, st);
+  return conv_wgrad_dispatch<float>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, flops, st);
 }
 
 bool wgrad_update_fusable(const ConvShape& s, int dt, bool bias) {
@@ -2055,8 +2052,10 @@ bool wgrad_update_fusable(const ConvShape& s, int dt, bool bias) {
 hipError_t launch_conv_wgrad_reduce_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
                                         float* dw, float* db, const SgdTargets& u, double flops, hipStream_t st) {
   if (!partial) return hipErrorNotSupported;
-  if (dt == BF16) return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
-  return conv_wgrad_dispatch<float>(s, x, dy, partial, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
+  const size_t pb = wgrad_partial_bytes(s, dt, u.b != nullptr, false);
+  if (dt == BF16)
+    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
+  return conv_wgrad_dispatch<float>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
 }
 
 hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* dw, float* db,
@@ -2065,7 +2064,7 @@ hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, cons
     return hipErrorNotSupported;
   // never a rewritten geometry: the GEMM's work is the layer's
   const double flops = 2.0 * s.N * (double)s.P * s.Q * s.K * (double)s.R * s.S * s.C;
-  return conv_wgrad_dispatch<bf16_t>(s, x, dy, nullptr, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
+  return conv_wgrad_dispatch<bf16_t>(s, x, dy, nullptr, 0, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
 }
 
 }  // namespace singa

@@ -65,9 +65,12 @@ hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const v
 // workspace; NULL when that is 0) and a second kernel adds them in a fixed
 // order.  `flops` is the algorithmic work of the layer pass this launch
 // carries out (s may be a rewritten geometry with zero taps).
-size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias);
-hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial, float* dw,
-                             float* db, int acc_dw, int acc_db, double flops, hipStream_t st);
+// least: the smallest size that works (an fp32 layer then makes fewer splits
+// than it would like: partial_bytes is what the partial tiles may take).
+size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least);
+hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
+                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, double flops,
+                             hipStream_t st);
 
 // Parameters the filter-gradient kernel updates in place once a gradient
 // element is complete (SGD with momentum, one step per element): the fp32

@@ -44,7 +44,9 @@ extern "C" int singa_conv_bwd_filter_noalloc(singa_dtype dtype, singa_layout lay
   size_t need = 0;
   int rc = singa_conv_workspace_bytes(SINGA_OP_BWD_FILTER, dtype, layout, x, w, d, &need);
   if (rc != SINGA_OK) return rc;
-  if (need > (size_t)SINGA_NOALLOC_SCRATCH_BYTES) return SINGA_ERR_SCRATCH;
+  // a size past the array's: the call below takes what fits (fewer splits of
+  // the reduction), or returns SINGA_ERR_WORKSPACE when that is too little
+  if (need > (size_t)SINGA_NOALLOC_SCRATCH_BYTES) need = SINGA_NOALLOC_SCRATCH_BYTES;
   void* ws = nullptr;
   if (need > 0) {
     int cur = -1;
@@ -57,5 +59,6 @@ extern "C" int singa_conv_bwd_filter_noalloc(singa_dtype dtype, singa_layout lay
     rc = scratch_address(cur, &ws);
     if (rc != SINGA_OK) return rc;
   }
-  return singa_conv_bwd_filter(dtype, layout, x, x_ptr, w, d, dy_ptr, dw, db, accumulate, ws, need, stream);
+  rc = singa_conv_bwd_filter(dtype, layout, x, x_ptr, w, d, dy_ptr, dw, db, accumulate, ws, need, stream);
+  return rc == SINGA_ERR_WORKSPACE ? SINGA_ERR_SCRATCH : rc;
 }

@@ -109,3 +109,69 @@ def test_source_gradient_tile(case, dt):
     got = dev_to_nchw(dx)
     np.testing.assert_array_equal(got[xr <= 0], 0.0)
     assert rel_l2(got, ref) <= TOL[dt]
+
+
+# the fp32 filter gradient's tiles: rows of the tile, how the reduction is
+# summed, whether a K-tile is 32 images at one pixel, and the layer (strided
+# and channel-padded ones among them)
+WGRAD_CASES = [
+    (32, "one", 0, (1, 44, 3, 15, 28, 3, 3, 1, 1)),
+    (32, "one", 1, (32, 148, 7, 1, 20, 1, 1, 0, 1)),
+    (32, "split", 0, (8, 4, 7, 20, 92, 1, 1, 0, 1)),
+    (32, "split", 1, (64, 28, 14, 5, 4, 1, 1, 0, 1)),
+    (64, "one", 0, (1, 116, 5, 1, 404, 5, 5, 2, 1)),
+    (64, "one", 1, (32, 156, 2, 1, 280, 5, 5, 2, 1)),
+    (64, "split", 0, (31, 4, 6, 12, 392, 1, 1, 0, 1)),
+    (64, "split", 1, (32, 4, 4, 18, 344, 1, 1, 0, 1)),
+    (128, "one", 0, (5, 156, 1, 24, 520, 5, 5, 2, 1)),
+    (128, "split", 0, (12, 4, 22, 20, 444, 1, 1, 0, 1)),
+    (128, "split", 1, (32, 4, 15, 24, 184, 1, 1, 0, 1)),
+    (32, "split", 0, (3, 3, 32, 32, 32, 5, 5, 2, 1)),    # 3 channels padded to 4
+    (32, "split", 0, (5, 32, 15, 17, 24, 3, 3, 1, 2)),   # stride 2
+]
+
+
+@pytest.mark.parametrize("bias", [True, False], ids=["bias", "no-bias"])
+@pytest.mark.parametrize("rows,how,nfast,case", WGRAD_CASES,
+                         ids=["%d-%s-%d-" % c[:3] + "x".join(map(str, c[3])) for c in WGRAD_CASES])
+def test_f32_filter_gradient_tile(rows, how, nfast, case, bias):
+    N, C, H, W, K, R, S, pad, stride = case
+    x, w, _ = _data(case, "f32", 320)
+    P, Q = oracle.conv_out(H, R, pad, stride), oracle.conv_out(W, S, pad, stride)
+    dy = wl.random_array((N, K, P, Q), 323, "normal", 1.0, "f32")
+    xd, dyd = nchw_to_dev(x, "f32"), nchw_to_dev(dy, "f32")
+    ref_dw, ref_db = oracle.conv_bwd_filter(x, dy, w.shape, pad=pad, stride=stride)
+    wshape = (K, R, S, C)
+    singa.trace_enable(True)
+    dw, db = singa.conv_bwd_filter(xd, dyd, wshape, pad, stride, with_bias=bias)
+    torch.cuda.synchronize()
+    names = [r[0] for r in singa.trace_records()]
+    singa.trace_enable(False)
+    assert "conv_wgrad_kernel<f32,%dx128,%d>" % (rows, nfast) in names, names
+    assert ("splitk_reduce_kernel" in names) == (how == "split"), names
+    assert rel_l2(dw.cpu().numpy().transpose(0, 3, 1, 2), ref_dw) <= TOL["f32"]
+    # accumulated: once more on top, and through the fixed scratch array
+    singa.conv_bwd_filter(xd, dyd, wshape, pad, stride, dw=dw, db=db, accumulate=True, with_bias=bias)
+    dn, bn = singa.conv_bwd_filter_noalloc(xd, dyd, wshape, pad, stride, with_bias=bias)
+    torch.cuda.synchronize()
+    assert rel_l2(dw.cpu().numpy().transpose(0, 3, 1, 2), 2 * ref_dw) <= TOL["f32"]
+    assert rel_l2(dn.cpu().numpy().transpose(0, 3, 1, 2), ref_dw) <= TOL["f32"]
+    if bias:
+        assert rel_l2(db.cpu().numpy(), 2 * ref_db) <= TOL["f32"]
+        assert rel_l2(bn.cpu().numpy(), ref_db) <= TOL["f32"]
+
+
+def test_f32_filter_gradient_least_workspace():
+    """A workspace of the size that the least number of partial tiles takes
+    (what the register-staged kernel's split rule asks for) is still enough."""
+    N, C, H, W, K, R, S, pad, stride = case = (2, 96, 19, 19, 144, 5, 5, 0, 1)  # 450 pixels: that rule has one split
+    x, w, _ = _data(case, "f32", 330)
+    dy = wl.random_array((N, K, 15, 15), 333, "normal", 1.0, "f32")
+    xd, dyd = nchw_to_dev(x, "f32"), nchw_to_dev(dy, "f32")
+    assert singa.conv_workspace_bytes(singa.OP_BWD_FILTER, torch.float32, phys(x.shape), (K, R, S, C), pad, stride) > 0
+    ref_dw, ref_db = oracle.conv_bwd_filter(x, dy, w.shape, pad=pad, stride=stride)
+    ws = torch.empty(16, dtype=torch.uint8, device="cuda")
+    dw, db = singa.conv_bwd_filter(xd, dyd, (K, R, S, C), pad, stride, workspace=ws)
+    torch.cuda.synchronize()
+    assert rel_l2(dw.cpu().numpy().transpose(0, 3, 1, 2), ref_dw) <= TOL["f32"]
+    assert rel_l2(db.cpu().numpy(), ref_db) <= TOL["f32"]
