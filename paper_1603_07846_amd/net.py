@@ -37,7 +37,6 @@ layers below; the backward loop ends by joining the two streams.
 """
 from __future__ import annotations
 
-import contextlib
 from typing import Dict, List, Optional
 
 import numpy as np
@@ -83,6 +82,7 @@ class ConvLayer(Layer):
         self.out_shape = singa.conv_out_shape(self.in_shape, self.w_shape, self.pad, self.stride)
         self.relu = False  # set when a ReLU layer directly follows and is fused
         self.relu_src = None  # the ReLU layer feeding this one, whose backward bwd-data folds in
+        self.event = None  # see _fork
         dev, dt = net.device, net.dtype
         # update fused into the filter-gradient kernel (no workspace needed exactly then)
         self.fused_update = bool(net.fuse_update and net.wl.update and net.updater == "sgd" and singa.conv_workspace_bytes(
@@ -140,14 +140,14 @@ class ConvLayer(Layer):
             # backward passes of the layers below (which read neither this
             # layer's weights nor write its x or dy)
             if side is not None:
-                side.wait_stream(torch.cuda.current_stream(net.device))
-            with torch.cuda.stream(side) if side is not None else contextlib.nullcontext():
-                singa.conv_bwd_filter_sgd(
-                    self.x, dy, self.w_shape, self.w, self.v, self.w_compute if net.wb_flat is not None else None,
-                    b=self.b, vb=self.vb, b_bf16=self.b_compute, lr=wl_.lr, momentum=wl_.momentum,
-                    weight_decay=wl_.weight_decay, pad=self.pad, stride=self.stride,
-                    dw=self.dw if keep else None,
-                    db=self.db if keep else None, workspace=net.workspace if side is None else net.workspace_wgrad)
+                self._fork()
+            singa.conv_bwd_filter_sgd(
+                self.x, dy, self.w_shape, self.w, self.v, self.w_compute if net.wb_flat is not None else None,
+                b=self.b, vb=self.vb, b_bf16=self.b_compute, lr=wl_.lr, momentum=wl_.momentum,
+                weight_decay=wl_.weight_decay, pad=self.pad, stride=self.stride,
+                dw=self.dw if keep else None,
+                db=self.db if keep else None, workspace=net.workspace if side is None else net.workspace_wgrad,
+                on=side)
             return self.dx if need_dx else None
         side = self.net.wgrad_stream
         if side is None or (not need_dx and self.net.last_wgrad_on_main):
@@ -160,12 +160,19 @@ class ConvLayer(Layer):
         else:
             # the filter gradient on the second stream, beside this layer's
             # backward-data and the layers below (both only read dy and x)
-            side.wait_stream(torch.cuda.current_stream(self.net.device))
-            with torch.cuda.stream(side):
-                singa.conv_bwd_filter(self.x, dy, self.w_shape, self.pad, self.stride, with_bias=self.has_bias,
-                                      dw=self.dw, db=self.db, workspace=self.net.workspace_wgrad,
-                                      layout=self.x_layout, x_shape=self.in_shape)
+            self._fork()
+            singa.conv_bwd_filter(self.x, dy, self.w_shape, self.pad, self.stride, with_bias=self.has_bias,
+                                  dw=self.dw, db=self.db, workspace=self.net.workspace_wgrad,
+                                  layout=self.x_layout, x_shape=self.in_shape, on=side)
         return self._bwd_data(dy, need_dx)
+
+    def _fork(self):
+        """The second stream waits for what the current one has been given so
+        far (an event of the layer's own, recorded anew each step)."""
+        if self.event is None:
+            self.event = torch.cuda.Event()
+        self.event.record(self.net.main_stream or torch.cuda.current_stream(self.net.device))
+        self.net.wgrad_stream.wait_event(self.event)
 
     def _bwd_data(self, dy, need_dx):
         if not need_dx:
@@ -336,6 +343,7 @@ class Net:
         self.workspace = singa.empty((max(self.ws_bytes, 256),), torch.uint8, self.device)
         # default priority, like every stream the library runs on
         self.wgrad_stream = None
+        self.main_stream = None  # the current stream, looked up once per backward pass
         if concurrent_wgrad and self.device.type == "cuda" and any(isinstance(l, ConvLayer) for l in self.layers):
             self.wgrad_stream = torch.cuda.Stream(device=self.device)
             self.workspace_wgrad = singa.empty((max(self.ws_wgrad_bytes, 256),), torch.uint8, self.device)
@@ -432,6 +440,7 @@ class Net:
         unless defer_join (train_one_batch with side_update): then update()
         issues the second-stream update and joins."""
         g = dy_top
+        self.main_stream = torch.cuda.current_stream(self.device) if self.wgrad_stream is not None else None
         side_after = (self.side_update_layers[0]
                       if defer_join and self.side_update_layers and self.wgrad_stream is not None else None)
         self._issued = None
@@ -440,9 +449,10 @@ class Net:
             if self.layers[i] is side_after:
                 # every backward-data pass that reads those layers' weights is issued
                 self._issued = torch.cuda.Event()
-                self._issued.record(torch.cuda.current_stream(self.device))
+                self._issued.record(self.main_stream)
         if self.wgrad_stream is not None and self._issued is None:
-            torch.cuda.current_stream(self.device).wait_stream(self.wgrad_stream)
+            self.main_stream.wait_stream(self.wgrad_stream)
+        self.main_stream = None
         return g
 
     def update(self):

@@ -13,6 +13,7 @@ fp32 tensors are torch.float32, bf16 tensors torch.bfloat16.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -106,13 +107,19 @@ def _lib():
                                              vp]
         lib.singa_sgd_momentum_update.argtypes = [sz, vp, vp, vp, vp, ctypes.c_float, ctypes.c_float,
                                                   ctypes.c_float, vp]
+        lib.singa_space_to_depth_bytes.argtypes = [i32, S4, F4, CD, ctypes.POINTER(sz)]
+        lib.singa_space_to_depth.argtypes = [i32, S4, vp, F4, CD, vp, vp]
         lib.singa_trace_enable.argtypes = [i32]
         lib.singa_trace_count.argtypes = []
         lib.singa_trace_get.argtypes = [i32, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_double),
                                         ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i32)]
         for name in EXPORTS:
+            fn = getattr(lib, name)
+            # pointers go in as Python integers, which ctypes would cut to 32
+            # bits in a call without declared arguments
+            assert fn.argtypes is not None, name
             if name != "singa_strerror":
-                getattr(lib, name).restype = i32
+                fn.restype = i32
         _LIB = lib
     return _LIB
 
@@ -158,11 +165,20 @@ def _dt(t: torch.Tensor) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The current stream's handle by torch's own short cut, a fifth of the time of
+# torch.cuda.current_stream(): a call of this module costs the host several
+# times its kernels' launches, which is what small layers wait for.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _pair(v) -> Tuple[int, int]:
@@ -207,41 +223,86 @@ def _cdesc(pad, stride) -> ConvDesc:
     return ConvDesc(ph, pw, sh, sw)
 
 
+class _ConvPlan:
+    """The C structs of one convolution geometry, what follows from it alone
+    (the output's physical shape) and, per operation, its workspace size.
+    Read-only once made."""
+
+    def __init__(self, dt, lay, xs, ws, pad, stride):
+        self._x, self._w, self._d = _act_shape4(xs, lay), _filt4(ws, lay), ConvDesc(*pad, *stride)
+        self.x, self.w, self.d = ctypes.byref(self._x), ctypes.byref(self._w), ctypes.byref(self._d)
+        self._sizes = (dt, lay)
+        y = Shape4()
+        _check("singa_conv_out_shape", _lib().singa_conv_out_shape(self.x, self.w, self.d, ctypes.byref(y)))
+        self.y_shape = _phys(y, NHWC if lay == NHWC_S2D else lay)
+
+    def workspace_bytes(self, op) -> int:
+        out = ctypes.c_size_t(0)
+        _check("singa_conv_workspace_bytes", _lib().singa_conv_workspace_bytes(
+            op, *self._sizes, self.x, self.w, self.d, ctypes.byref(out)))
+        return out.value
+
+
+# Shapes repeat from call to call; a failed check raises and keeps nothing.
+@functools.lru_cache(maxsize=1024)
+def _conv_plan(dt, lay, xs, ws, pad, stride) -> _ConvPlan:
+    return _ConvPlan(dt, lay, xs, ws, pad, stride)
+
+
+@functools.lru_cache(maxsize=1024)
+def _conv_op(op, dt, lay, xs, ws, pad, stride):
+    """(plan, workspace bytes) of one operation."""
+    plan = _conv_plan(dt, lay, xs, ws, pad, stride)
+    return plan, plan.workspace_bytes(op)
+
+
 def conv_out_shape(x_shape, w_shape, pad=0, stride=1, layout="NHWC"):
     """Physical output shape of a convolution."""
-    lay = _layout(layout)
-    y = Shape4()
-    _check("singa_conv_out_shape", _lib().singa_conv_out_shape(
-        ctypes.byref(_act_shape4(x_shape, lay)), ctypes.byref(_filt4(w_shape, lay)),
-        ctypes.byref(_cdesc(pad, stride)), ctypes.byref(y)))
-    return _phys(y, lay)
+    return _conv_plan(F32, _layout(layout), tuple(x_shape), tuple(w_shape), _pair(pad), _pair(stride)).y_shape
+
+
+def _pdesc(mode, k, stride, pad, ceil_mode) -> PoolDesc:
+    kh, kw = _pair(k)
+    sh, sw = _pair(stride)
+    ph, pw = _pair(pad)
+    m = POOL_MAX if mode in (POOL_MAX, "max") else POOL_AVG
+    return PoolDesc(m, kh, kw, sh, sw, ph, pw, int(bool(ceil_mode)))
+
+
+@functools.lru_cache(maxsize=1024)
+def _pool_plan(lay, xs, m, k, stride, pad, ceil_mode):
+    """(input extents, descriptor, output's physical shape) of a pooling."""
+    x, d, y = _act_shape4(xs, lay), _pdesc(m, k, stride, pad, ceil_mode), Shape4()
+    _check("singa_pool_out_shape", _lib().singa_pool_out_shape(ctypes.byref(x), ctypes.byref(d), ctypes.byref(y)))
+    return ctypes.byref(x), ctypes.byref(d), _phys(y, lay)
+
+
+def _pool_key(lay, xs, mode, k, stride, pad, ceil_mode):
+    m = POOL_MAX if mode in (POOL_MAX, "max") else POOL_AVG
+    return m, _pool_plan(lay, tuple(xs), m, _pair(k), _pair(stride), _pair(pad), int(bool(ceil_mode)))
 
 
 def pool_out_shape(x_shape, mode, k=3, stride=2, pad=0, ceil_mode=True, layout="NHWC"):
-    lay = _layout(layout)
-    y = Shape4()
-    _check("singa_pool_out_shape", _lib().singa_pool_out_shape(
-        ctypes.byref(_act_shape4(x_shape, lay)), ctypes.byref(_pdesc(mode, k, stride, pad, ceil_mode)),
-        ctypes.byref(y)))
-    return _phys(y, lay)
+    return _pool_key(_layout(layout), x_shape, mode, k, stride, pad, ceil_mode)[1][2]
 
 
 def conv_workspace_bytes(op, dtype, x_shape, w_shape, pad=0, stride=1, layout="NHWC") -> int:
-    lay = _layout(layout)
     dt = dtype if isinstance(dtype, int) else (BF16 if dtype == torch.bfloat16 else F32)
-    out = ctypes.c_size_t(0)
-    _check("singa_conv_workspace_bytes", _lib().singa_conv_workspace_bytes(
-        op, dt, lay, ctypes.byref(_act_shape4(x_shape, lay)), ctypes.byref(_filt4(w_shape, lay)),
-        ctypes.byref(_cdesc(pad, stride)), ctypes.byref(out)))
-    return int(out.value)
+    return _conv_op(op, dt, _layout(layout), tuple(x_shape), tuple(w_shape), _pair(pad), _pair(stride))[1]
 
 
-def _workspace(nbytes, device, ws):
+def _new(shape, dtype, device, on):
+    if on is not None:
+        raise ValueError("a call on another stream needs its outputs and workspace given")
+    return empty(shape, dtype, device)
+
+
+def _workspace(nbytes, device, ws, on=None):
     if nbytes == 0:
         return None
     if ws is not None:
         return ws
-    return empty((nbytes,), torch.uint8, device)
+    return _new((nbytes,), torch.uint8, device, on)
 
 
 def space_to_depth_shape(x_shape, w_shape, pad=0, stride=1):
@@ -266,11 +327,11 @@ def space_to_depth_bytes(dtype, x_shape, w_shape, pad=0, stride=1) -> int:
 def space_to_depth(x, w_shape, pad=0, stride=1, out=None):
     """The space-to-depth form of the NHWC input x of a strided convolution
     (layout "NHWC_S2D" of conv_fwd / conv_bwd_filter, with x_shape=x.shape)."""
-    shape = space_to_depth_shape(tuple(x.shape), tuple(w_shape), pad, stride)
-    xs = empty(shape, x.dtype, x.device) if out is None else out
+    dt = _dt(x)
+    plan = _conv_plan(dt, NHWC, x.shape, tuple(w_shape), _pair(pad), _pair(stride))
+    xs = empty(space_to_depth_shape(x.shape, w_shape, pad, stride), x.dtype, x.device) if out is None else out
     _check("singa_space_to_depth", _lib().singa_space_to_depth(
-        _dt(x), ctypes.byref(_act_shape4(x.shape, NHWC)), _ptr(x), ctypes.byref(_filt4(w_shape, NHWC)),
-        ctypes.byref(_cdesc(pad, stride)), _ptr(xs), _stream()))
+        dt, plan.x, _ptr(x), plan.w, plan.d, _ptr(xs), _stream()))
     return xs
 
 
@@ -278,15 +339,13 @@ def conv_fwd(x, w, bias=None, pad=0, stride=1, relu=False, layout="NHWC", out=No
     """Convolution ComputeFeature: y = [relu](conv(x, w) + bias).  With layout
     "NHWC_S2D", x is space_to_depth()'s output and x_shape the NHWC shape of
     the input it was made from."""
-    lay = _layout(layout)
-    xs = tuple(x.shape) if lay != NHWC_S2D else tuple(x_shape)
-    yshape = conv_out_shape(xs, tuple(w.shape), pad, stride, NHWC if lay == NHWC_S2D else lay)
-    y = empty(yshape, x.dtype, x.device) if out is None else out
-    nbytes = conv_workspace_bytes(OP_FWD, _dt(x), xs, tuple(w.shape), pad, stride, lay)
+    lay, dt = _layout(layout), _dt(x)
+    xs = x.shape if lay != NHWC_S2D else tuple(x_shape)
+    plan, nbytes = _conv_op(OP_FWD, dt, lay, xs, w.shape, _pair(pad), _pair(stride))
+    y = empty(plan.y_shape, x.dtype, x.device) if out is None else out
     ws = _workspace(nbytes, x.device, workspace)
     _check("singa_conv_fwd", _lib().singa_conv_fwd(
-        _dt(x), lay, ctypes.byref(_act_shape4(xs, lay)), _ptr(x), ctypes.byref(_filt4(w.shape, lay)), _ptr(w),
-        _ptr(bias), ctypes.byref(_cdesc(pad, stride)), _ptr(y), int(bool(relu)), _ptr(ws),
+        dt, lay, plan.x, _ptr(x), plan.w, _ptr(w), _ptr(bias), plan.d, _ptr(y), int(bool(relu)), _ptr(ws),
         0 if ws is None else ws.numel(), _stream()))
     return y
 
@@ -297,35 +356,36 @@ def conv_bwd_data(dy, w, x_shape, pad=0, stride=1, layout="NHWC", out=None, work
     relu_y: the output of a ReLU that is the source layer (shape x_shape); the
     result is then the gradient at that ReLU's input (its ComputeGradient
     folded into this call)."""
-    lay = _layout(layout)
+    lay, dt = _layout(layout), _dt(dy)
     dx = empty(tuple(x_shape), dy.dtype, dy.device) if out is None else out
-    nbytes = conv_workspace_bytes(OP_BWD_DATA, _dt(dy), tuple(x_shape), tuple(w.shape), pad, stride, lay)
+    plan, nbytes = _conv_op(OP_BWD_DATA, dt, lay, tuple(x_shape), w.shape, _pair(pad), _pair(stride))
     ws = _workspace(nbytes, dy.device, workspace)
     _check("singa_conv_bwd_data", _lib().singa_conv_bwd_data(
-        _dt(dy), lay, ctypes.byref(_act_shape4(x_shape, lay)), ctypes.byref(_filt4(w.shape, lay)), _ptr(w),
-        ctypes.byref(_cdesc(pad, stride)), _ptr(dy), _ptr(relu_y), _ptr(dx), _ptr(ws),
+        dt, lay, plan.x, plan.w, _ptr(w), plan.d, _ptr(dy), _ptr(relu_y), _ptr(dx), _ptr(ws),
         0 if ws is None else ws.numel(), _stream()))
     return dx
 
 
 def conv_bwd_filter(x, dy, w_shape, pad=0, stride=1, layout="NHWC", with_bias=True, dw=None, db=None,
-                    accumulate=False, workspace=None, x_shape=None):
+                    accumulate=False, workspace=None, x_shape=None, on=None):
     """Convolution ComputeGradient, Param gradients (fp32 dw and db).  With
     layout "NHWC_S2D", x is space_to_depth()'s output and x_shape the NHWC
-    shape of the input it was made from."""
+    shape of the input it was made from.  on: a stream to run on instead of
+    the current one (dw, db and the workspace then have to be given: what is
+    allocated here belongs to the current stream)."""
     lay = _layout(layout)
-    xs = tuple(x.shape) if lay != NHWC_S2D else tuple(x_shape)
+    xs = x.shape if lay != NHWC_S2D else tuple(x_shape)
     if dw is None:
-        dw = empty(tuple(w_shape), torch.float32, x.device)
+        dw = _new(tuple(w_shape), torch.float32, x.device, on)
     if with_bias and db is None:
-        k = w_shape[0]
-        db = empty((k,), torch.float32, x.device)
-    nbytes = conv_workspace_bytes(OP_BWD_FILTER, _dt(x), xs, tuple(w_shape), pad, stride, lay)
-    ws = _workspace(nbytes, x.device, workspace)
+        db = _new((w_shape[0],), torch.float32, x.device, on)
+    dt = _dt(x)
+    plan, nbytes = _conv_op(OP_BWD_FILTER, dt, lay, xs, tuple(w_shape), _pair(pad), _pair(stride))
+    ws = _workspace(nbytes, x.device, workspace, on)
     _check("singa_conv_bwd_filter", _lib().singa_conv_bwd_filter(
-        _dt(x), lay, ctypes.byref(_act_shape4(xs, lay)), _ptr(x), ctypes.byref(_filt4(w_shape, lay)),
-        ctypes.byref(_cdesc(pad, stride)), _ptr(dy), _ptr(dw), _ptr(db if with_bias else None),
-        int(bool(accumulate)), _ptr(ws), 0 if ws is None else ws.numel(), _stream()))
+        dt, lay, plan.x, _ptr(x), plan.w, plan.d, _ptr(dy), _ptr(dw), _ptr(db if with_bias else None),
+        int(bool(accumulate)), _ptr(ws), 0 if ws is None else ws.numel(),
+        _stream() if on is None else on.cuda_stream))
     return dw, (db if with_bias else None)
 
 
@@ -348,42 +408,31 @@ def conv_bwd_filter_noalloc(x, dy, w_shape, pad=0, stride=1, layout="NHWC", with
 
 
 def conv_bwd_filter_sgd(x, dy, w_shape, w, v, w_bf16=None, b=None, vb=None, b_bf16=None, lr=0.01, momentum=0.9,
-                        weight_decay=0.0, pad=0, stride=1, layout="NHWC", dw=None, db=None, workspace=None):
+                        weight_decay=0.0, pad=0, stride=1, layout="NHWC", dw=None, db=None, workspace=None, on=None):
     """Param gradients of a convolution with the momentum SGD step applied to
     them at once: w, v (fp32, filter shape) and w_bf16 updated in place, the
     bias likewise when b is given; dw / db, if given, also receive the
-    gradient.  Returns (w, v)."""
-    lay = _layout(layout)
-    nbytes = conv_workspace_bytes(OP_BWD_FILTER_SGD, _dt(x), tuple(x.shape), tuple(w_shape), pad, stride, lay)
-    ws = _workspace(nbytes, x.device, workspace)
+    gradient.  on: as for conv_bwd_filter.  Returns (w, v)."""
+    lay, dt = _layout(layout), _dt(x)
+    plan, nbytes = _conv_op(OP_BWD_FILTER_SGD, dt, lay, x.shape, tuple(w_shape), _pair(pad), _pair(stride))
+    ws = _workspace(nbytes, x.device, workspace, on)
     _check("singa_conv_bwd_filter_sgd", _lib().singa_conv_bwd_filter_sgd(
-        _dt(x), lay, ctypes.byref(_act_shape4(x.shape, lay)), _ptr(x), ctypes.byref(_filt4(w_shape, lay)),
-        ctypes.byref(_cdesc(pad, stride)), _ptr(dy), _ptr(dw), _ptr(db), _ptr(w), _ptr(v), _ptr(w_bf16), _ptr(b),
-        _ptr(vb), _ptr(b_bf16), float(lr), float(momentum), float(weight_decay), _ptr(ws),
-        0 if ws is None else ws.numel(), _stream()))
+        dt, lay, plan.x, _ptr(x), plan.w, plan.d, _ptr(dy), _ptr(dw), _ptr(db), _ptr(w), _ptr(v), _ptr(w_bf16),
+        _ptr(b), _ptr(vb), _ptr(b_bf16), float(lr), float(momentum), float(weight_decay), _ptr(ws),
+        0 if ws is None else ws.numel(), _stream() if on is None else on.cuda_stream))
     return w, v
-
-
-def _pdesc(mode, k, stride, pad, ceil_mode) -> PoolDesc:
-    kh, kw = _pair(k)
-    sh, sw = _pair(stride)
-    ph, pw = _pair(pad)
-    m = POOL_MAX if mode in (POOL_MAX, "max") else POOL_AVG
-    return PoolDesc(m, kh, kw, sh, sw, ph, pw, int(bool(ceil_mode)))
 
 
 def pool_fwd(x, mode, k=3, stride=2, pad=0, ceil_mode=True, layout="NHWC", out=None, argmax=None):
     """Pooling ComputeFeature; returns (y, argmax) (argmax is None for AVG)."""
     lay = _layout(layout)
-    d = _pdesc(mode, k, stride, pad, ceil_mode)
-    yshape = pool_out_shape(tuple(x.shape), mode, k, stride, pad, ceil_mode, lay)
+    m, (xd, d, yshape) = _pool_key(lay, x.shape, mode, k, stride, pad, ceil_mode)
     y = empty(yshape, x.dtype, x.device) if out is None else out
-    if d.mode == POOL_MAX and argmax is None:
+    if m == POOL_MAX and argmax is None:
         argmax = empty(yshape, torch.uint8, x.device)
     _check("singa_pool_fwd", _lib().singa_pool_fwd(
-        _dt(x), lay, ctypes.byref(_act_shape4(x.shape, lay)), _ptr(x), ctypes.byref(d), _ptr(y),
-        _ptr(argmax if d.mode == POOL_MAX else None), _stream()))
-    return y, (argmax if d.mode == POOL_MAX else None)
+        _dt(x), lay, xd, _ptr(x), d, _ptr(y), _ptr(argmax if m == POOL_MAX else None), _stream()))
+    return y, (argmax if m == POOL_MAX else None)
 
 
 def pool_bwd(dy, argmax, x_shape, mode, k=3, stride=2, pad=0, ceil_mode=True, layout="NHWC", out=None, relu_y=None):
@@ -391,11 +440,10 @@ def pool_bwd(dy, argmax, x_shape, mode, k=3, stride=2, pad=0, ceil_mode=True, la
     when its input is a ReLU's output; the result is then the gradient at that
     ReLU's input."""
     lay = _layout(layout)
-    d = _pdesc(mode, k, stride, pad, ceil_mode)
+    m, (xd, d, _) = _pool_key(lay, x_shape, mode, k, stride, pad, ceil_mode)
     dx = empty(tuple(x_shape), dy.dtype, dy.device) if out is None else out
     _check("singa_pool_bwd", _lib().singa_pool_bwd(
-        _dt(dy), lay, ctypes.byref(_act_shape4(x_shape, lay)), ctypes.byref(d), _ptr(dy),
-        _ptr(argmax if d.mode == POOL_MAX else None), _ptr(relu_y), _ptr(dx), _stream()))
+        _dt(dy), lay, xd, d, _ptr(dy), _ptr(argmax if m == POOL_MAX else None), _ptr(relu_y), _ptr(dx), _stream()))
     return dx
 
 
@@ -414,7 +462,8 @@ def relu_bwd(y, dy, out=None):
 def softmax_ce(z, labels, loss=None, dz=None):
     """Softmax cross-entropy over rows of z (batch, classes); returns (loss, dz) where
     loss is an fp32 tensor of batch + 1 values: the mean, then each row's loss."""
-    B, classes = z.shape[0], z[0].numel()
+    B = z.shape[0]
+    classes = z.numel() // B if B else z[0].numel()
     loss = empty((B + 1,), torch.float32, z.device) if loss is None else loss
     dz = empty(z.shape, z.dtype, z.device) if dz is None else dz
     _check("singa_softmax_ce", _lib().singa_softmax_ce(_dt(z), B, classes, _ptr(z), _ptr(labels), _ptr(loss),
@@ -430,13 +479,17 @@ def sgd_momentum_update(w, g, v, w_bf16=None, lr=0.01, momentum=0.9, weight_deca
     return w, v
 
 
+@functools.lru_cache(maxsize=256)
+def _lrn_plan(lay, xs, size, alpha, beta, k):
+    return ctypes.byref(_act_shape4(xs, lay)), ctypes.byref(LrnDesc(size, alpha, beta, k))
+
+
 def lrn_fwd(x, size=5, alpha=1e-4, beta=0.75, k=1.0, layout="NHWC", out=None):
     """Local response normalization across channels (Caffe's form)."""
     lay = _layout(layout)
     y = empty(x.shape, x.dtype, x.device) if out is None else out
-    _check("singa_lrn_fwd", _lib().singa_lrn_fwd(
-        _dt(x), lay, ctypes.byref(_act_shape4(x.shape, lay)), _ptr(x),
-        ctypes.byref(LrnDesc(int(size), float(alpha), float(beta), float(k))), _ptr(y), _stream()))
+    xd, d = _lrn_plan(lay, x.shape, int(size), float(alpha), float(beta), float(k))
+    _check("singa_lrn_fwd", _lib().singa_lrn_fwd(_dt(x), lay, xd, _ptr(x), d, _ptr(y), _stream()))
     return y
 
 
@@ -444,9 +497,8 @@ def lrn_bwd(x, dy, size=5, alpha=1e-4, beta=0.75, k=1.0, layout="NHWC", out=None
     """Gradient of sum(dy * lrn_fwd(x)) with respect to x."""
     lay = _layout(layout)
     dx = empty(x.shape, x.dtype, x.device) if out is None else out
-    _check("singa_lrn_bwd", _lib().singa_lrn_bwd(
-        _dt(x), lay, ctypes.byref(_act_shape4(x.shape, lay)), _ptr(x), _ptr(dy),
-        ctypes.byref(LrnDesc(int(size), float(alpha), float(beta), float(k))), _ptr(dx), _stream()))
+    xd, d = _lrn_plan(lay, x.shape, int(size), float(alpha), float(beta), float(k))
+    _check("singa_lrn_bwd", _lib().singa_lrn_bwd(_dt(x), lay, xd, _ptr(x), _ptr(dy), d, _ptr(dx), _stream()))
     return dx
 
 
