@@ -194,8 +194,7 @@ hipError_t conv_fwd_nhwc(int dt, const ConvShape& s, const void* x, const void* 
   if (rw == RW_NONE) return launch_conv_fwd(dt, s, x, w, bias, y, relu, 0, conv_flops(s), o.partial, nullptr, st);
   hipError_t e;
   if (rw == RW_PAD) {
-    e = launch_pad_channels(dt, x, o.xp, (long)s.N * s.H * s.W, s.C, g.C, st);
-    if (e == hipSuccess) e = launch_pad_channels(dt, w, o.wp, (long)s.K * s.R * s.S, s.C, g.C, st);
+    e = launch_pad_channels(dt, x, o.xp, (long)s.N * s.H * s.W, w, o.wp, (long)s.K * s.R * s.S, s.C, g.C, st);
   } else {
     e = x_s2d ? hipSuccess : launch_space_to_depth(dt, s, g, x, o.xp, st);
     if (e == hipSuccess) e = launch_filter_to_s2d(dt, s, g, w, o.wp, st);
@@ -521,20 +520,28 @@ int singa_conv_bwd_filter(singa_dtype dtype, singa_layout layout, const singa_sh
   // g: the GEMM's geometry (input rewritten when input_rewrite says so)
   ConvShape g;
   const Rewrite rw = input_rewrite(s, dtype, &g);
-  if (rw == RW_PAD && e == hipSuccess) e = launch_pad_channels(dtype, xx, o.xp, (long)s.N * s.H * s.W, s.C, g.C, st);
+  if (rw == RW_PAD && e == hipSuccess) e = launch_pad_channels(dtype, xx, o.xp, (long)s.N * s.H * s.W, nullptr, nullptr, 0, s.C, g.C, st);
   if (rw == RW_S2D && e == hipSuccess && layout != SINGA_NHWC_S2D) e = launch_space_to_depth(dtype, s, g, xx, o.xp, st);
   if (rw != RW_NONE && layout != SINGA_NHWC_S2D) xx = o.xp;
-  float* krsc = layout != SINGA_NCHW ? dw : o.dw;  // KRSC result
-  const int acc = layout != SINGA_NCHW ? accumulate : 0;
-  float* target = rw != RW_NONE ? o.dwp : krsc;  // the GEMM's (K, g.R, g.S, g.C) result
-  const int tacc = rw != RW_NONE ? 0 : acc;
+  // The GEMM's result (K, g.R, g.S, g.C) goes to the caller's filter through
+  // the map of its reduction; in one piece it is staged and moved on.
+  const bool nchw = layout == SINGA_NCHW, mapped = nchw || rw != RW_NONE;
+  const int RSC = s.R * s.S * s.C;
+  const FilterMap map{make_fastdiv((uint32_t)g.C), make_fastdiv((uint32_t)g.S), make_fastdiv((uint32_t)s.C),
+                      make_fastdiv((uint32_t)(rw == RW_S2D ? s.sw : 1)), rw == RW_S2D ? s.sh : 1, s.R, s.S, RSC,
+                      nchw ? s.S : s.S * s.C, nchw ? 1 : s.C, nchw ? s.R * s.S : 1};
+  float* krsc = nchw ? o.dw : dw;  // staged: the KRSC result
+  const int acc = nchw ? 0 : accumulate;
+  int staged = 0;
   // db is written in place by the GEMM's bias column, with the caller's accumulate
   if (e == hipSuccess)
-    e = launch_conv_wgrad(dtype, g, xx, dy, o.partial, o.partial_bytes, target, db, tacc, accumulate, conv_flops(s), st);
+    e = launch_conv_wgrad(dtype, g, xx, dy, o.partial, o.partial_bytes, dw, db, accumulate, accumulate,
+                          mapped ? &map : nullptr, rw != RW_NONE ? o.dwp : krsc, &staged, conv_flops(s), st);
+  if (!staged) return hip_status(e);
   if (e == hipSuccess && rw == RW_PAD)
     e = launch_unpad_channels_f32(o.dwp, krsc, (long)s.K * s.R * s.S, g.C, s.C, acc, st);
   if (e == hipSuccess && rw == RW_S2D) e = launch_s2d_to_filter_f32(s, g, o.dwp, krsc, acc, st);
-  if (e == hipSuccess && layout == SINGA_NCHW) e = launch_krsc_to_kcrs_f32(o.dw, dw, s.K, s.C, s.R, s.S, accumulate, st);
+  if (e == hipSuccess && nchw) e = launch_krsc_to_kcrs_f32(o.dw, dw, s.K, s.C, s.R, s.S, accumulate, st);
   return hip_status(e);
 }
 

@@ -174,45 +174,65 @@ __global__ __launch_bounds__(256) void krsc_to_kcrs_kernel(const float* __restri
   }
 }
 
-// out[r][c] = in[r][c] for c < C, 0 for C <= c < Cp (Cp % 4 == 0): one
-// thread per 4-channel chunk of an output row, stored as one vector.
+// out[r][c] = in[r][c] for c < C, 0 for C <= c < Cp (Cp % 4 == 0), over two
+// tensors in one launch (an input and its filter: a launch each, with another
+// for the rows that an 8-row group left over, took longer than the work).
+// A workgroup below `split` works on the first tensor, the others on the
+// second; one thread per 4-channel chunk of an output row, stored as one vector.
+template <typename T> struct PadSpan {
+  const T* in;
+  T* out;
+  long rows;
+};
 template <typename T>
-__global__ __launch_bounds__(256) void pad_channels_kernel(const T* __restrict__ in, T* __restrict__ out, long rows,
-                                                           int C, int Cp) {
+__global__ __launch_bounds__(256) void pad_channels_kernel(PadSpan<T> a, PadSpan<T> b, unsigned split, int C, int Cp) {
   typedef typename std::conditional<sizeof(T) == 2, uint2, uint4>::type V4;
+  const bool first = blockIdx.x < split;
+  const PadSpan<T> p = first ? a : b;
+  const long blk = first ? blockIdx.x : blockIdx.x - split, nblk = first ? split : gridDim.x - split;
   const int nv = Cp / 4;
-  const long total = rows * nv;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
+  const long total = p.rows * nv;
+  for (long i = blk * blockDim.x + threadIdx.x; i < total; i += nblk * blockDim.x) {
     const long r = i / nv;
     const int c0 = (int)(i - r * nv) * 4;
     union { V4 u; T e[4]; } v;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v.e[j] = (c0 + j < C) ? in[r * C + c0 + j] : (T)0;
-    *(V4*)(out + r * Cp + c0) = v.u;
+    for (int j = 0; j < 4; ++j) v.e[j] = (c0 + j < C) ? p.in[r * C + c0 + j] : (T)0;
+    *(V4*)(p.out + r * Cp + c0) = v.u;
   }
 }
 
 // The same for C = 3, Cp = 4 (colour images): one thread per 8 rows, read as
-// 3 (bf16) / 6 (fp32) 16-byte vectors and written as 4 / 8.
+// 3 (bf16) / 6 (fp32) 16-byte vectors and written as 4 / 8; the thread after
+// the last whole group takes the rows left over one by one.
 template <typename T>
-__global__ __launch_bounds__(256) void pad_3to4_kernel(const T* __restrict__ in, T* __restrict__ out, long groups) {
+__global__ __launch_bounds__(256) void pad_3to4_kernel(PadSpan<T> a, PadSpan<T> b, unsigned split) {
   constexpr int NI = 24 * (int)sizeof(T) / 16, NO = 32 * (int)sizeof(T) / 16;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < groups; i += (long)gridDim.x * blockDim.x) {
-    union { uint4 u[NI]; T e[24]; } a;
-    union { uint4 u[NO]; T e[32]; } b;
-    const uint4* src = (const uint4*)(in + i * 24);
-#pragma unroll
-    for (int k = 0; k < NI; ++k) a.u[k] = src[k];
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      b.e[4 * p] = a.e[3 * p];
-      b.e[4 * p + 1] = a.e[3 * p + 1];
-      b.e[4 * p + 2] = a.e[3 * p + 2];
-      b.e[4 * p + 3] = T(0);
+  const bool first = blockIdx.x < split;
+  const PadSpan<T> p = first ? a : b;
+  const long blk = first ? blockIdx.x : blockIdx.x - split, nblk = first ? split : gridDim.x - split;
+  const long groups = p.rows / 8;
+  for (long i = blk * blockDim.x + threadIdx.x; i <= groups; i += nblk * blockDim.x) {
+    if (i == groups) {
+      for (long r = groups * 8; r < p.rows; ++r)
+        for (int c = 0; c < 4; ++c) p.out[r * 4 + c] = c < 3 ? p.in[r * 3 + c] : T(0);
+      break;
     }
-    uint4* dst = (uint4*)(out + i * 32);
+    union { uint4 u[NI]; T e[24]; } s;
+    union { uint4 u[NO]; T e[32]; } d;
+    const uint4* src = (const uint4*)(p.in + i * 24);
 #pragma unroll
-    for (int k = 0; k < NO; ++k) dst[k] = b.u[k];
+    for (int k = 0; k < NI; ++k) s.u[k] = src[k];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      d.e[4 * q] = s.e[3 * q];
+      d.e[4 * q + 1] = s.e[3 * q + 1];
+      d.e[4 * q + 2] = s.e[3 * q + 2];
+      d.e[4 * q + 3] = T(0);
+    }
+    uint4* dst = (uint4*)(p.out + i * 32);
+#pragma unroll
+    for (int k = 0; k < NO; ++k) dst[k] = d.u[k];
   }
 }
 
@@ -377,32 +397,23 @@ hipError_t launch_conv_bwd_data_direct(int dt, const ConvShape& s, const void* d
   return hipGetLastError();
 }
 
-hipError_t launch_pad_channels(int dt, const void* in, void* out, long rows, int C, int Cp, hipStream_t st) {
+template <typename T>
+static void pad_channels(const void* in, void* out, long rows, const void* in2, void* out2, long rows2, int C, int Cp,
+                         hipStream_t st) {
+  const PadSpan<T> a{(const T*)in, (T*)out, rows}, b{(const T*)in2, (T*)out2, rows2};
+  const bool v = C == 3 && Cp == 4 && (((uintptr_t)in | (uintptr_t)out | (uintptr_t)in2 | (uintptr_t)out2) % 16) == 0;
+  const long items = v ? rows / 8 + 1 : rows * (Cp / 4), items2 = v ? rows2 / 8 + 1 : rows2 * (Cp / 4);
+  const unsigned split = grid_for(items), grid = split + (rows2 > 0 ? grid_for(items2) : 0);
+  if (v) hipLaunchKernelGGL(pad_3to4_kernel<T>, dim3(grid), dim3(256), 0, st, a, b, split);
+  else hipLaunchKernelGGL(pad_channels_kernel<T>, dim3(grid), dim3(256), 0, st, a, b, split, C, Cp);
+}
+
+hipError_t launch_pad_channels(int dt, const void* in, void* out, long rows, const void* in2, void* out2, long rows2,
+                               int C, int Cp, hipStream_t st) {
   if (Cp % 4 != 0 || C > Cp) return hipErrorInvalidValue;
-  TraceScope ts("pad_channels_kernel", st, (double)rows * (C + Cp) * dt_size(dt), WORK_BYTE);
-  const long groups = rows / 8;
-  if (C == 3 && Cp == 4 && groups > 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)out % 16 == 0) {
-    // vector body over whole groups of 8 rows, generic kernel for the tail
-    if (dt == BF16)
-      hipLaunchKernelGGL(pad_3to4_kernel<bf16_t>, dim3(grid_for(groups)), dim3(256), 0, st, (const bf16_t*)in,
-                         (bf16_t*)out, groups);
-    else
-      hipLaunchKernelGGL(pad_3to4_kernel<float>, dim3(grid_for(groups)), dim3(256), 0, st, (const float*)in,
-                         (float*)out, groups);
-    const long done = groups * 8;
-    if (done == rows) return hipGetLastError();
-    const size_t es = dt_size(dt);
-    in = (const char*)in + done * C * es;
-    out = (char*)out + done * Cp * es;
-    rows -= done;
-  }
-  const long total = rows * (Cp / 4);
-  if (dt == BF16)
-    hipLaunchKernelGGL(pad_channels_kernel<bf16_t>, dim3(grid_for(total)), dim3(256), 0, st, (const bf16_t*)in,
-                       (bf16_t*)out, rows, C, Cp);
-  else
-    hipLaunchKernelGGL(pad_channels_kernel<float>, dim3(grid_for(total)), dim3(256), 0, st, (const float*)in,
-                       (float*)out, rows, C, Cp);
+  TraceScope ts("pad_channels_kernel", st, (double)(rows + rows2) * (C + Cp) * dt_size(dt), WORK_BYTE);
+  if (dt == BF16) pad_channels<bf16_t>(in, out, rows, in2, out2, rows2, C, Cp, st);
+  else pad_channels<float>(in, out, rows, in2, out2, rows2, C, Cp, st);
   return hipGetLastError();
 }
 

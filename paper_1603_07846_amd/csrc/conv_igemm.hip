@@ -1396,11 +1396,16 @@ __global__ __launch_bounds__(UPD ? NT : 2 * NT, 2) void conv_wgrad_large_kernel(
 // group 0 adds the G partial sums in group order, so the result does not
 // depend on timing.  Many splits (the first layer's long reduction over few
 // filter elements) take G = 16, so the grid still fills the chip.
-template <int G, bool UPD>
+// MAP: dw is the caller's filter, laid out or shaped otherwise than the GEMM's
+// columns (channel-padded or space-to-depth input, KCRS filters): element
+// (row, col) goes where `map` says, and columns that are only padding are
+// dropped.  This replaces a pass that read and wrote the whole gradient (5 us
+// of AlexNet's first layer, 4 of a small one) by three integer divisions.
+template <int G, bool UPD, bool MAP>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int M,
                                                             int ldp, int Ng, int Nn, float* __restrict__ dw,
                                                             float* __restrict__ db, int acc_dw, int acc_db,
-                                                            SgdTargets u) {
+                                                            SgdTargets u, FilterMap map) {
   constexpr int LG = 256 / G;
   __shared__ float4 part[G][LG];
   const size_t n = (size_t)M * ldp;
@@ -1442,7 +1447,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
       const int ce = col + e;
       if (ce >= Ng) break;
       const bool is_w = ce < Nn;
-      const size_t o = is_w ? (size_t)row * Nn + ce : (size_t)row;
+      size_t o = is_w ? (size_t)row * Nn + ce : (size_t)row;
+      if constexpr (MAP) {
+        if (is_w) {
+          const int q = (int)fdiv((uint32_t)ce, map.dCg), cs = ce - q * (int)map.dCg.d;
+          const int rg = (int)fdiv((uint32_t)q, map.dSg), sg = q - rg * (int)map.dSg.d;
+          const int d = (int)fdiv((uint32_t)cs, map.dC), ch = cs - d * (int)map.dC.d;
+          const int dh = (int)fdiv((uint32_t)d, map.dsw), dv = d - dh * (int)map.dsw.d;
+          const int r = map.sh * rg + dh, s = (int)map.dsw.d * sg + dv;
+          if (dh >= map.sh || r >= map.R || s >= map.S) continue;
+          o = (size_t)row * map.row + (size_t)r * map.r + (size_t)s * map.s + (size_t)ch * map.c;
+        }
+      }
       if constexpr (UPD) {
         // the Updater's step on the complete gradient element; dw / db (may
         // be NULL) also receive the gradient
@@ -1903,11 +1919,35 @@ int wgrad_splits_for(const ConvShape& s, int dt, bool bias, bool large) {
   return wgrad_split_count(tiles, (T + bk - 1) / bk, 1024);  // about 4 workgroups per CU
 }
 
+// The kernel that runs the filter gradient of s and its splits.
+struct WgradChoice {
+  bool large, tile;    // the 128 x 256 bf16 kernel, the fp32 tile kernel
+  WgradTilePlan plan;  // (tile: which one), splits
+};
+WgradChoice wgrad_choose(const ConvShape& s, int dt, bool va, int vb, size_t partial_bytes, bool bias) {
+  WgradChoice c;
+  c.large = wgrad_large_shape(s, dt) && va && vb == VEC16;
+  c.tile = dt == F32 && va && vb == VEC16;
+  const long Ng = (long)s.R * s.S * s.C + (bias ? 1 : 0);
+  if (c.tile) {
+    const long max_splits = (long)(partial_bytes / ((size_t)s.K * ((Ng + 63) / 64 * 64) * sizeof(float)));
+    c.plan = wgrad_tile_plan(s.K, Ng, (long)s.N * s.P * s.Q, max_splits);
+  } else {
+    c.plan = WgradTilePlan{0, wgrad_splits_for(s, dt, bias, c.large), false};
+  }
+  return c;
+}
+
+int wgrad_splits(int dt, const ConvShape& s, const void* x, const void* dy, size_t partial_bytes, bool bias) {
+  const bool va = s.K % (dt == BF16 ? 8 : 4) == 0 && (uintptr_t)dy % 16 == 0;
+  const int vb = dt == BF16 ? load_mode<bf16_t>(s.C, x) : load_mode<float>(s.C, x);
+  return wgrad_choose(s, dt, va, vb, partial_bytes, bias).plan.splits;
+}
+
 template <typename T>
 hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy, float* partial,
-                               size_t partial_bytes, float* dw,
-                               float* db, int acc_dw, int acc_db, const SgdTargets* upd, double flops,
-                               hipStream_t st) {
+                               size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db,
+                               const SgdTargets* upd, const FilterMap* map, double flops, hipStream_t st) {
   constexpr int VEC = 16 / (int)sizeof(T);
   constexpr int DT = sizeof(T) == 2 ? BF16 : F32;
   WgradArgs a;
@@ -1926,19 +1966,18 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
   a.dS = make_fastdiv((uint32_t)s.S);
   const bool va = (a.M % VEC) == 0 && ((uintptr_t)dy % 16) == 0;
   const int vb = load_mode<T>(s.C, x);
-  const bool large = wgrad_large_shape(s, DT) && va && vb == VEC16;
-  const bool tile = sizeof(T) == 4 && va && vb == VEC16;  // the fp32 tile kernel
   const bool bias = upd ? upd->b != nullptr : db != nullptr;
   a.Ng = a.Nn + (bias ? 1 : 0);
   a.ldp = (a.Ng + 63) / 64 * 64;
-  const long max_splits = (long)(partial_bytes / ((size_t)a.M * a.ldp * sizeof(float)));
-  WgradTilePlan plan = tile ? wgrad_tile_plan(a.M, a.Ng, a.T, max_splits) : WgradTilePlan{0, 1, false};
+  const WgradChoice ch = wgrad_choose(s, DT, va, vb, partial_bytes, bias);
+  const bool large = ch.large, tile = ch.tile;
+  WgradTilePlan plan = ch.plan;
   const int bm = large ? WL_BM : tile ? wgrad_tile_rows(plan.tile) : BM, bn = large ? WL_BN : BN;
   const int bk = large ? WL_BK : WG<T>::BK;
   a.nkt = (a.T + bk - 1) / bk;
   a.tiles_n = (a.Ng + bn - 1) / bn;
   a.tiles = ((a.M + bm - 1) / bm) * a.tiles_n;
-  const int splits = tile ? plan.splits : wgrad_splits_for(s, DT, bias, large);
+  const int splits = plan.splits;
   // the update goes into the large kernel when it writes each element once,
   // otherwise into the split-K reduction; a single split of the 128 x 128
   // kernel has no place for it
@@ -1980,25 +2019,18 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
   // fixed-order sum of the partial tiles into dw (and db), or, with the
   // update, the Updater's step on each summed element
   const size_t n = (size_t)a.M * a.ldp;
+  const double bytes = (double)a.M * a.Ng * (4.0 * splits + (upd ? 18.0 + (dw ? 4.0 : 0.0) : acc_dw ? 8.0 : 4.0));
+  TraceScope ts(upd ? "splitk_reduce_sgd_kernel" : "splitk_reduce_kernel", st, bytes, WORK_BYTE);
   const SgdTargets none{};
-  if (upd) {
-    const double bytes = (double)a.M * a.Ng * (4.0 * splits + 18.0 + (dw ? 4.0 : 0.0));
-    TraceScope ts("splitk_reduce_sgd_kernel", st, bytes, WORK_BYTE);
-    if (splits >= 64)
-      hipLaunchKernelGGL((splitk_reduce_kernel<16, true>), dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial,
-                         splits, a.M, a.ldp, a.Ng, a.Nn, dw, db, 0, 0, *upd);
-    else
-      hipLaunchKernelGGL((splitk_reduce_kernel<4, true>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, partial,
-                         splits, a.M, a.ldp, a.Ng, a.Nn, dw, db, 0, 0, *upd);
-    return hipGetLastError();
-  }
-  TraceScope ts("splitk_reduce_kernel", st, (double)a.M * a.Ng * 4.0 * (splits + 1 + (acc_dw ? 1 : 0)), WORK_BYTE);
-  if (splits >= 64)
-    hipLaunchKernelGGL((splitk_reduce_kernel<16, false>), dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial,
-                       splits, a.M, a.ldp, a.Ng, a.Nn, dw, db, acc_dw, acc_db, none);
-  else
-    hipLaunchKernelGGL((splitk_reduce_kernel<4, false>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, partial,
-                       splits, a.M, a.ldp, a.Ng, a.Nn, dw, db, acc_dw, acc_db, none);
+  const FilterMap as_is{};
+#define REDUCE(G, U, MP)                                                                                         \
+  hipLaunchKernelGGL((splitk_reduce_kernel<G, U, MP>), dim3((unsigned)((n + 1024 / G - 1) / (1024 / G))), dim3(256), 0, \
+                     st, partial, splits, a.M, a.ldp, a.Ng, a.Nn, dw, db, U ? 0 : acc_dw, U ? 0 : acc_db,         \
+                     U ? *upd : none, MP ? *map : as_is)
+  if (upd) { if (splits >= 64) REDUCE(16, true, false); else REDUCE(4, true, false); }
+  else if (map) { if (splits >= 64) REDUCE(16, false, true); else REDUCE(4, false, true); }
+  else { if (splits >= 64) REDUCE(16, false, false); else REDUCE(4, false, false); }
+#undef REDUCE
   return hipGetLastError();
 }
 
@@ -2038,11 +2070,21 @@ size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least) {
 }
 
 hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
-                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, double flops,
-                             hipStream_t st) {
+                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, const FilterMap* map,
+                             float* staging, int* staged, double flops, hipStream_t st) {
+  // the reduction of the partial tiles applies the map; a gradient in one
+  // piece is written as the GEMM has it
+  const bool direct = wgrad_splits(dt, s, x, dy, partial_bytes, db != nullptr) == 1;
+  *staged = map && direct;
+  if (*staged) {
+    dw = staging;
+    acc_dw = 0;
+    map = nullptr;
+  }
   if (dt == BF16)
-    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, flops, st);
-  return conv_wgrad_dispatch<float>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, flops, st);
+    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, map, flops,
+                                       st);
+  return conv_wgrad_dispatch<float>(s, x, dy, partial, partial_bytes, dw, db, acc_dw, acc_db, nullptr, map, flops, st);
 }
 
 bool wgrad_update_fusable(const ConvShape& s, int dt, bool bias) {
@@ -2054,8 +2096,8 @@ hipError_t launch_conv_wgrad_reduce_sgd(int dt, const ConvShape& s, const void* 
   if (!partial) return hipErrorNotSupported;
   const size_t pb = wgrad_partial_bytes(s, dt, u.b != nullptr, false);
   if (dt == BF16)
-    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
-  return conv_wgrad_dispatch<float>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
+    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, nullptr, flops, st);
+  return conv_wgrad_dispatch<float>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, nullptr, flops, st);
 }
 
 hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* dw, float* db,
@@ -2064,7 +2106,7 @@ hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, cons
     return hipErrorNotSupported;
   // never a rewritten geometry: the GEMM's work is the layer's
   const double flops = 2.0 * s.N * (double)s.P * s.Q * s.K * (double)s.R * s.S * s.C;
-  return conv_wgrad_dispatch<bf16_t>(s, x, dy, nullptr, 0, dw, u.b ? db : nullptr, 0, 0, &u, flops, st);
+  return conv_wgrad_dispatch<bf16_t>(s, x, dy, nullptr, 0, dw, u.b ? db : nullptr, 0, 0, &u, nullptr, flops, st);
 }
 
 }  // namespace singa

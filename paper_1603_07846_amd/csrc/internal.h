@@ -9,6 +9,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "common.h"
+
 namespace singa {
 
 enum Dt { F32 = 0, BF16 = 1 };
@@ -58,6 +60,16 @@ size_t fwd_partial_bytes(const ConvShape& s, int dt);
 hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const void* wt, void* y, int bwd,
                               double flops, float* partial, const void* mask, hipStream_t st);
 
+// Where column ((r' Sg + s') Cg + (dh sw + dw) C + c) of a filter-gradient GEMM
+// goes in the caller's filter: element (r, s, c), r = sh r' + dh, s = sw s' +
+// dw, at row * row + r * r + s * s + c * c (element strides); columns with
+// dh >= sh, r >= R or s >= S are padding.  Channel padding: sh = sw = 1, C < Cg.
+struct FilterMap {
+  FastDiv dCg, dSg, dC, dsw;
+  int sh, R, S;
+  long row, r, s, c;
+};
+
 // Split-K implicit-GEMM filter gradient, dw (K, R, S, C) and, with db, the
 // bias gradient from one more GEMM column against ones.  With one split the
 // kernel writes (or, with acc_dw / acc_db, adds into) dw and db directly;
@@ -68,9 +80,13 @@ hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const v
 // least: the smallest size that works (an fp32 layer then makes fewer splits
 // than it would like: partial_bytes is what the partial tiles may take).
 size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least);
+// map: dw is laid out or shaped otherwise than the GEMM's (K, g.R, g.S, g.C)
+// result (see FilterMap).  The reduction of the partial tiles writes it there;
+// a gradient in one piece goes to `staging` as the GEMM has it, not
+// accumulated, and *staged is set: the caller moves it on.
 hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
-                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, double flops,
-                             hipStream_t st);
+                             size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, const FilterMap* map,
+                             float* staging, int* staged, double flops, hipStream_t st);
 
 // Parameters the filter-gradient kernel updates in place once a gradient
 // element is complete (SGD with momentum, one step per element): the fp32
@@ -119,9 +135,10 @@ hipError_t launch_transpose(int dt, const void* in, void* out, int batch, int ro
 hipError_t launch_conv_bwd_data_direct(int dt, const ConvShape& s, const void* dy, const void* w, void* dx,
                                        const void* mask, hipStream_t st);
 
-// Zero-pad the innermost (channel) dimension: in [rows][C] -> out [rows][Cp],
-// Cp a multiple of the 16-byte vector width.
-hipError_t launch_pad_channels(int dt, const void* in, void* out, long rows, int C, int Cp, hipStream_t st);
+// Zero-pad the innermost (channel) dimension of one or two tensors: in [rows][C]
+// -> out [rows][Cp], Cp a multiple of 4 (rows2 = 0: one tensor).
+hipError_t launch_pad_channels(int dt, const void* in, void* out, long rows, const void* in2, void* out2, long rows2,
+                               int C, int Cp, hipStream_t st);
 // Space-to-depth rewrite of the strided convolution s as the stride-1,
 // unpadded convolution g (H, W, C, R, S of g are the rewritten ones): input,
 // filter, filter gradient (fp32, optionally accumulated) and input gradient
