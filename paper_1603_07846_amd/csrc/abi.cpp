@@ -409,7 +409,7 @@ int singa_conv_fwd(singa_dtype dtype, singa_layout layout, const singa_shape4* x
   hipError_t e = launch_nchw_to_nhwc(dtype, x_ptr, o.x, s.N, s.C, s.H, s.W, st);
   if (e == hipSuccess) e = kcrs_to_krsc(dtype, s, w_ptr, o.w, st);
   if (e == hipSuccess) e = conv_fwd_nhwc(dtype, s, o.x, o.w, bias, o.y, fuse_relu, o, st);
-  if (e == hipSuccess) e = launch_nhwc_to_nchw(dtype, o.y, y_ptr, s.N, s.K, s.P, s.Q, st);
+  if (e == hipSuccess) e = launch_nhwc_to_nchw(dtype, o.y, y_ptr, s.N, s.K, s.P, s.Q, nullptr, st);
   return hip_status(e);
 }
 
@@ -425,7 +425,7 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
   if (!aligned_to(w_ptr, es) || !aligned_to(dy_ptr, es) || !aligned_to(dx_ptr, es) || !aligned_to(ws, 16) ||
       !aligned_to(relu_y, es))
     return SINGA_ERR_ALIGN;
-  // NCHW applies the ReLU mask with the vectorized ReLU-backward kernel
+  // (an NCHW call's mask and result have to allow 16-byte vectors)
   if (relu_y && layout == SINGA_NCHW && (!aligned_to(relu_y, 16) || !aligned_to(dx_ptr, 16)))
     return SINGA_ERR_ALIGN;
   BwdDataWs o;
@@ -440,7 +440,8 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
   const void* nhwc_mask = layout == SINGA_NHWC ? relu_y : nullptr;  // folded into the producing kernel
   if (layout == SINGA_NCHW) {
     e = launch_nchw_to_nhwc(dtype, dy_ptr, o.dy, s.N, s.K, s.P, s.Q, st);
-    if (e == hipSuccess) e = kcrs_to_krsc(dtype, s, w_ptr, o.w, st);
+    // a unit-stride layer's flipped copy is made from the KCRS filter itself
+    if (e == hipSuccess && (bwd_data_fc(s) || !bwd_data_gemm(s))) e = kcrs_to_krsc(dtype, s, w_ptr, o.w, st);
     dy = o.dy;
     wk = o.w;
     dx = o.dx;
@@ -467,6 +468,8 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
         if (bwd_data_fc(s)) {
           const int J = RS * s.C;  // wt[(r,s,c)][k] = w[k][(r,s,c)]
           e = launch_transpose(dtype, wk, o.wt, 1, s.K, J, 0, J, 0, s.K, 0, st);
+        } else if (layout == SINGA_NCHW) {  // wt[c][r'][s'][k] = w[k][c][R-1-r'][S-1-s']
+          e = launch_transpose(dtype, w_ptr, o.wt, s.C, s.K, RS, RS, (long)s.C * RS, (long)RS * s.K, s.K, 2, st);
         } else {  // wt[c][r'][s'][k] = w[k][R-1-r'][S-1-s'][c]
           e = launch_transpose(dtype, wk, o.wt, RS, s.K, s.C, s.C, (long)RS * s.C, s.K, (long)RS * s.K, 1, st);
         }
@@ -478,10 +481,8 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
       e = launch_conv_bwd_data_direct(dtype, s, dy, wk, dx, nhwc_mask, st);
     }
   }
-  if (e == hipSuccess && layout == SINGA_NCHW) {
-    e = launch_nhwc_to_nchw(dtype, dx, dx_ptr, s.N, s.C, s.H, s.W, st);
-    if (e == hipSuccess && relu_y) e = launch_relu_bwd(dtype, act_bytes(s, dtype) / es, relu_y, dx_ptr, dx_ptr, st);
-  }
+  if (e == hipSuccess && layout == SINGA_NCHW)
+    e = launch_nhwc_to_nchw(dtype, dx, dx_ptr, s.N, s.C, s.H, s.W, relu_y, st);  // with the ReLU's backward
   return hip_status(e);
 }
 

@@ -21,64 +21,80 @@ template <typename T> __device__ __forceinline__ void st_f(T* p, float v);
 template <> __device__ __forceinline__ void st_f<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_f<bf16_t>(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 
-// 32 x 32 tile through LDS: reads are coalesced along cols, writes along rows.
-template <typename T>
+// Batched transpose of a 64 x 64 tile through LDS.  VIN: rows of the input
+// are read as 16-byte vectors (their length, stride and base allow it),
+// otherwise element by element, 64 consecutive columns per wave; VOUT: the
+// same for the rows written.  All loads of a tile are issued before the first
+// is used: with a 32 x 32 tile of four loads a thread the permutations of a
+// layer's activations between NCHW and NHWC moved 1.7-2 TB/s.  mask (optional,
+// laid out like the output): an element is zeroed where mask <= 0.  flip 1:
+// the batches go out in reverse order; 2: each batch's output rows do.
+template <typename T, bool VIN, bool VOUT>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int batch,
                                                         int rows, int cols, long in_bstride, long in_rstride,
-                                                        long out_bstride, long out_rstride, int flip) {
-  __shared__ T tile[32][33];
-  const int b = blockIdx.z;
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const T* src = in + (long)b * in_bstride;
-  T* dst = out + (long)(flip ? batch - 1 - b : b) * out_bstride;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int r = r0 + ty + k, c = c0 + tx;
-    if (r < rows && c < cols) tile[ty + k][tx] = src[(long)r * in_rstride + c];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int c = c0 + ty + k, r = r0 + tx;
-    if (r < rows && c < cols) dst[(long)c * out_rstride + r] = tile[tx][ty + k];
-  }
-}
-
-// Vector form for 16-byte aligned rows: a 64 x 64 tile, read as 16-byte row
-// vectors into LDS and written as 16-byte vectors of the transposed rows
-// (every stride, size and base a multiple of the vector width).
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_vec_kernel(const T* __restrict__ in, T* __restrict__ out, int batch,
-                                                            int rows, int cols, long in_bstride, long in_rstride,
-                                                            long out_bstride, long out_rstride, int flip) {
+                                                        long out_bstride, long out_rstride, int flip,
+                                                        const T* __restrict__ mask) {
   constexpr int VEC = 16 / (int)sizeof(T);
-  constexpr int TPR = 64 / VEC;   // threads per 64-element row
+  constexpr int TPR = 64 / VEC;   // threads per 64-element row of vectors
   constexpr int RPP = 256 / TPR;  // rows per pass
   __shared__ T tile[64][64 + 2];
   const int b = blockIdx.z;
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const T* src = in + (long)b * in_bstride;
-  T* dst = out + (long)(flip ? batch - 1 - b : b) * out_bstride;
+  const long ob = (long)(flip == 1 ? batch - 1 - b : b) * out_bstride;
   const int tc = threadIdx.x % TPR, tr = threadIdx.x / TPR;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if constexpr (VIN) {
+    union { uint4 u; T e[VEC]; } v[64 / RPP];
 #pragma unroll
-  for (int k = 0; k < 64; k += RPP) {
-    const int r = r0 + tr + k, c = c0 + tc * VEC;
-    union { uint4 u; T e[VEC]; } v;
-    if (r < rows && c < cols) v.u = *(const uint4*)(src + (long)r * in_rstride + c);
-    else v.u = make_uint4(0, 0, 0, 0);
+    for (int k = 0; k < 64 / RPP; ++k) {
+      const int r = r0 + tr + k * RPP, c = c0 + tc * VEC;
+      v[k].u = (r < rows && c < cols) ? *(const uint4*)(src + (long)r * in_rstride + c) : make_uint4(0, 0, 0, 0);
+    }
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) tile[tr + k][tc * VEC + j] = v.e[j];
+    for (int k = 0; k < 64 / RPP; ++k)
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) tile[tr + k * RPP][tc * VEC + j] = v[k].e[j];
+  } else {
+    T v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int r = r0 + wave + 4 * k, c = c0 + lane;
+      v[k] = (r < rows && c < cols) ? src[(long)r * in_rstride + c] : T(0);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) tile[wave + 4 * k][lane] = v[k];
   }
   __syncthreads();
+  if constexpr (VOUT) {
 #pragma unroll
-  for (int k = 0; k < 64; k += RPP) {
-    const int c = c0 + tr + k, r = r0 + tc * VEC;  // output row c, output columns r .. r + VEC - 1
-    if (c < cols && r < rows) {
-      union { uint4 u; T e[VEC]; } v;
+    for (int k = 0; k < 64 / RPP; ++k) {
+      const int c = c0 + tr + k * RPP, r = r0 + tc * VEC;  // output row c, output columns r .. r + VEC - 1
+      if (c < cols && r < rows) {
+        const long o = ob + (long)(flip == 2 ? cols - 1 - c : c) * out_rstride + r;
+        union { uint4 u; T e[VEC]; } v;
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) v.e[j] = tile[tc * VEC + j][tr + k];
-      *(uint4*)(dst + (long)c * out_rstride + r) = v.u;
+        for (int j = 0; j < VEC; ++j) v.e[j] = tile[tc * VEC + j][tr + k * RPP];
+        if (mask) {
+          union { uint4 u; T e[VEC]; } m;
+          m.u = *(const uint4*)(mask + o);
+#pragma unroll
+          for (int j = 0; j < VEC; ++j)
+            if (!(ld_f<T>(&m.e[j]) > 0.f)) v.e[j] = T(0);
+        }
+        *(uint4*)(out + o) = v.u;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int c = c0 + wave + 4 * k, r = r0 + lane;
+      if (c < cols && r < rows) {
+        const long o = ob + (long)(flip == 2 ? cols - 1 - c : c) * out_rstride + r;
+        T v = tile[lane][wave + 4 * k];
+        if (mask && !(ld_f<T>(mask + o) > 0.f)) v = T(0);
+        out[o] = v;
+      }
     }
   }
 }
@@ -116,47 +132,6 @@ __global__ __launch_bounds__(256) void bwd_data_direct_kernel(ConvShape s, const
     }
     if (mask && !(ld_f<T>(mask + i) > 0.f)) acc = 0.f;
     st_f<T>(dx + i, acc);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void nchw_to_nhwc_kernel(const T* __restrict__ in, T* __restrict__ out, int C,
-                                                           int HW) {
-  // one (n) image per blockIdx.z; transpose [C][HW] -> [HW][C] with 32x32 tiles
-  __shared__ T tile[32][33];
-  const long base = (long)blockIdx.z * C * HW;
-  const int c0 = blockIdx.y * 32, s0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int c = c0 + ty + k, sp = s0 + tx;
-    if (c < C && sp < HW) tile[ty + k][tx] = in[base + (long)c * HW + sp];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int sp = s0 + ty + k, c = c0 + tx;
-    if (c < C && sp < HW) out[base + (long)sp * C + c] = tile[tx][ty + k];
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const T* __restrict__ in, T* __restrict__ out, int C,
-                                                           int HW) {
-  __shared__ T tile[32][33];
-  const long base = (long)blockIdx.z * C * HW;
-  const int s0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int sp = s0 + ty + k, c = c0 + tx;
-    if (c < C && sp < HW) tile[ty + k][tx] = in[base + (long)sp * C + c];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 32; k += 8) {
-    int c = c0 + ty + k, sp = s0 + tx;
-    if (c < C && sp < HW) out[base + (long)c * HW + sp] = tile[tx][ty + k];
   }
 }
 
@@ -357,28 +332,29 @@ unsigned grid_for(long total, int block = 256, long cap = 65536) {
 
 }  // namespace
 
+template <typename T>
+static void transpose(const void* in, void* out, int batch, int rows, int cols, long in_bstride, long in_rstride,
+                      long out_bstride, long out_rstride, int flip, const void* mask, hipStream_t st) {
+  constexpr long V = 16 / (long)sizeof(T);
+  const bool vin = cols % V == 0 && in_rstride % V == 0 && in_bstride % V == 0 && (uintptr_t)in % 16 == 0;
+  const bool vout = rows % V == 0 && out_rstride % V == 0 && out_bstride % V == 0 &&
+                    (((uintptr_t)out | (uintptr_t)mask) % 16) == 0;
+  const dim3 grid((cols + 63) / 64, (rows + 63) / 64, batch), block(256);
+#define TRANSPOSE(I, O)                                                                                              \
+  hipLaunchKernelGGL((transpose_kernel<T, I, O>), grid, block, 0, st, (const T*)in, (T*)out, batch, rows, cols,      \
+                     in_bstride, in_rstride, out_bstride, out_rstride, flip, (const T*)mask)
+  if (vin) { if (vout) TRANSPOSE(true, true); else TRANSPOSE(true, false); }
+  else { if (vout) TRANSPOSE(false, true); else TRANSPOSE(false, false); }
+#undef TRANSPOSE
+}
+
 hipError_t launch_transpose(int dt, const void* in, void* out, int batch, int rows, int cols, long in_bstride,
                             long in_rstride, long out_bstride, long out_rstride, int flip, hipStream_t st) {
   TraceScope ts("transpose_kernel", st, 2.0 * batch * (double)rows * cols * dt_size(dt), WORK_BYTE);
-  const long vec = 16 / (long)dt_size(dt);
-  if (rows % vec == 0 && cols % vec == 0 && in_rstride % vec == 0 && out_rstride % vec == 0 &&
-      in_bstride % vec == 0 && out_bstride % vec == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)out % 16 == 0) {
-    dim3 g64((cols + 63) / 64, (rows + 63) / 64, batch);
-    if (dt == BF16)
-      hipLaunchKernelGGL(transpose_vec_kernel<bf16_t>, g64, dim3(256), 0, st, (const bf16_t*)in, (bf16_t*)out, batch,
-                         rows, cols, in_bstride, in_rstride, out_bstride, out_rstride, flip);
-    else
-      hipLaunchKernelGGL(transpose_vec_kernel<float>, g64, dim3(256), 0, st, (const float*)in, (float*)out, batch,
-                         rows, cols, in_bstride, in_rstride, out_bstride, out_rstride, flip);
-    return hipGetLastError();
-  }
-  dim3 grid((cols + 31) / 32, (rows + 31) / 32, batch), block(256);
   if (dt == BF16)
-    hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, batch, rows,
-                       cols, in_bstride, in_rstride, out_bstride, out_rstride, flip);
+    transpose<bf16_t>(in, out, batch, rows, cols, in_bstride, in_rstride, out_bstride, out_rstride, flip, nullptr, st);
   else
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, block, 0, st, (const float*)in, (float*)out, batch, rows,
-                       cols, in_bstride, in_rstride, out_bstride, out_rstride, flip);
+    transpose<float>(in, out, batch, rows, cols, in_bstride, in_rstride, out_bstride, out_rstride, flip, nullptr, st);
   return hipGetLastError();
 }
 
@@ -485,23 +461,18 @@ hipError_t launch_depth_to_space(int dt, const ConvShape& s, const ConvShape& g,
 
 hipError_t launch_nchw_to_nhwc(int dt, const void* in, void* out, int N, int C, int H, int W, hipStream_t st) {
   const int HW = H * W;
-  dim3 grid((HW + 31) / 32, (C + 31) / 32, N), block(256);
   TraceScope ts("nchw_to_nhwc_kernel", st, 2.0 * N * (double)C * HW * dt_size(dt), WORK_BYTE);
-  if (dt == BF16)
-    hipLaunchKernelGGL(nchw_to_nhwc_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, C, HW);
-  else
-    hipLaunchKernelGGL(nchw_to_nhwc_kernel<float>, grid, block, 0, st, (const float*)in, (float*)out, C, HW);
+  if (dt == BF16) transpose<bf16_t>(in, out, N, C, HW, (long)C * HW, HW, (long)C * HW, C, 0, nullptr, st);
+  else transpose<float>(in, out, N, C, HW, (long)C * HW, HW, (long)C * HW, C, 0, nullptr, st);
   return hipGetLastError();
 }
 
-hipError_t launch_nhwc_to_nchw(int dt, const void* in, void* out, int N, int C, int H, int W, hipStream_t st) {
+hipError_t launch_nhwc_to_nchw(int dt, const void* in, void* out, int N, int C, int H, int W, const void* mask,
+                               hipStream_t st) {
   const int HW = H * W;
-  dim3 grid((C + 31) / 32, (HW + 31) / 32, N), block(256);
-  TraceScope ts("nhwc_to_nchw_kernel", st, 2.0 * N * (double)C * HW * dt_size(dt), WORK_BYTE);
-  if (dt == BF16)
-    hipLaunchKernelGGL(nhwc_to_nchw_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, C, HW);
-  else
-    hipLaunchKernelGGL(nhwc_to_nchw_kernel<float>, grid, block, 0, st, (const float*)in, (float*)out, C, HW);
+  TraceScope ts("nhwc_to_nchw_kernel", st, (mask ? 3.0 : 2.0) * N * (double)C * HW * dt_size(dt), WORK_BYTE);
+  if (dt == BF16) transpose<bf16_t>(in, out, N, HW, C, (long)C * HW, C, (long)C * HW, HW, 0, mask, st);
+  else transpose<float>(in, out, N, HW, C, (long)C * HW, C, (long)C * HW, HW, 0, mask, st);
   return hipGetLastError();
 }
 

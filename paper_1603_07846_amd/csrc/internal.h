@@ -126,7 +126,8 @@ hipError_t launch_conv_wgrad_reduce_sgd(int dt, const ConvShape& s, const void* 
 
 // Batched 2-D transpose: for b in [0, batch): out(b)[c][r] = in(b)[r][c] with
 // in(b) = in + in_base(b), out(b) = out + out_base(b), where
-// in_base(b) = b * in_bstride and out_base(b) = (flip ? batch-1-b : b) * out_bstride.
+// in_base(b) = b * in_bstride and out_base(b) = (flip == 1 ? batch-1-b : b) * out_bstride;
+// flip == 2: out(b)[cols-1-c][r] = in(b)[r][c] instead.
 hipError_t launch_transpose(int dt, const void* in, void* out, int batch, int rows, int cols,
                             long in_bstride, long in_rstride, long out_bstride, long out_rstride,
                             int flip, hipStream_t st);
@@ -156,7 +157,9 @@ hipError_t launch_unpad_channels_f32(const float* in, float* out, long rows, int
 
 // NCHW <-> NHWC permutations for the NCHW entry points.
 hipError_t launch_nchw_to_nhwc(int dt, const void* in, void* out, int N, int C, int H, int W, hipStream_t st);
-hipError_t launch_nhwc_to_nchw(int dt, const void* in, void* out, int N, int C, int H, int W, hipStream_t st);
+// mask (NCHW, optional): an element is zeroed where mask <= 0 (a ReLU's backward).
+hipError_t launch_nhwc_to_nchw(int dt, const void* in, void* out, int N, int C, int H, int W, const void* mask,
+                               hipStream_t st);
 // fp32 filter gradient KRSC -> KCRS, with optional accumulation into out.
 hipError_t launch_krsc_to_kcrs_f32(const float* in, float* out, int K, int C, int R, int S, int accumulate,
                                    hipStream_t st);
