@@ -291,6 +291,10 @@ struct FwdTilePlan {
 // segs: the pieces a bf16 GEMM's tap range is summed in (fp32 chooses its own).
 FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs);
 hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd, double flops, hipStream_t st);
+// A dense layer (P = Q = 1 and the window covers the whole input) of at most
+// three rows, operands in whole 16-byte vectors: a matrix-vector kernel.
+bool fwd_gemv_ok(const ConvShape& s);
+hipError_t launch_conv_fwd_gemv(int dt, const FwdArgs& a, int bwd, double flops, hipStream_t st);
 
 namespace {
 

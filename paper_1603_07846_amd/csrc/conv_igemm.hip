@@ -1738,6 +1738,7 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
   const int am = load_mode<T>(s.C, x);
   const int bm = wt ? BT16 : load_mode<T>(a.Kg, w);
   const bool vec16 = am == VEC16 && bm == VEC16;
+  if (vec16 && fwd_gemv_ok(s)) return launch_conv_fwd_gemv(sizeof(T) == 2 ? BF16 : F32, a, bwd, flops, st);
   const bool large = vec16 && sizeof(T) == 2 && use_large_fwd(a.M, a.Nn, a.Kg) && !tuning_env("SINGA_FWD_TILE");
   const int segs = fwd_splits_for(a.M, a.Nn, a.Kg, BK);
   const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, sizeof(T) == 2 ? BF16 : F32, segs)

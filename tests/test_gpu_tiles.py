@@ -175,3 +175,44 @@ def test_f32_filter_gradient_least_workspace():
     torch.cuda.synchronize()
     assert rel_l2(dw.cpu().numpy().transpose(0, 3, 1, 2), ref_dw) <= TOL["f32"]
     assert rel_l2(db.cpu().numpy(), ref_db) <= TOL["f32"]
+
+
+# dense layers of one to three rows: the matrix-vector kernel, at widths
+# around its four columns a workgroup and reductions around the 256 chunks
+# that it takes at a time; four rows take a tile
+GEMV_CASES = [(1, 16, 4, 4, 1), (2, 40, 1, 1, 7), (3, 8, 5, 3, 10), (1, 4096, 1, 1, 130), (2, 264, 4, 4, 33),
+              (3, 2048, 1, 1, 1000), (4, 2048, 1, 1, 100)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("relu", [False, True], ids=["", "relu"])
+@pytest.mark.parametrize("case", GEMV_CASES, ids=["x".join(map(str, c)) for c in GEMV_CASES])
+def test_dense_layer_of_few_rows(case, relu, dt):
+    N, C, H, W, K = case
+    x, w, b = _data((N, C, H, W, K, H, W, 0, 1), dt, 340)
+    singa.trace_enable(True)
+    y = singa.conv_fwd(nchw_to_dev(x, dt), kcrs_to_dev(w, dt), torch.from_numpy(b).cuda() if relu else None, 0, 1,
+                       relu=relu)
+    torch.cuda.synchronize()
+    names = [r[0] for r in singa.trace_records()]
+    singa.trace_enable(False)
+    assert (names == ["conv_fwd_kernel<%s,gemv,0>" % dt]) == (N <= 3), names
+    ref = oracle.conv_fwd(x, w, b if relu else None, pad=0, stride=1)
+    ref = oracle.relu_fwd(ref) if relu else ref
+    assert rel_l2(dev_to_nchw(y), ref) <= TOL[dt]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_source_gradient_of_few_rows(dt):
+    """fp32 backward-data runs the matrix-vector kernel on the transposed
+    weights, with the ReLU below folded in."""
+    N, C, H, W, K = 2, 24, 3, 3, 40
+    x, w, _ = _data((N, C, H, W, K, H, W, 0, 1), dt, 350)
+    xr = np.maximum(x, 0.0)
+    dy = wl.random_array((N, K, 1, 1), 353, "normal", 1.0, dt)
+    dx = singa.conv_bwd_data(nchw_to_dev(dy, dt), kcrs_to_dev(w, dt), phys(x.shape), 0, 1, relu_y=nchw_to_dev(xr, dt))
+    torch.cuda.synchronize()
+    ref = oracle.relu_bwd(xr, oracle.conv_bwd_data(dy, w, x.shape, pad=0, stride=1))
+    got = dev_to_nchw(dx)
+    np.testing.assert_array_equal(got[xr <= 0], 0.0)
+    assert rel_l2(got, ref) <= TOL[dt]
