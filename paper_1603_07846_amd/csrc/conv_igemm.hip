@@ -1001,8 +1001,9 @@ __global__ __launch_bounds__(NT) void conv_wgrad_kernel(WgradArgs a) {
 //
 // The same product for bf16 operands with whole 16-byte filter and tap chunks
 // (K % 8 == 0, C % 8 == 0), on a 128 (filters) x 256 (taps) tile: each of 8
-// waves owns 64 x 64 (2 x 2 blocks of 32 x 32), or, with the update fused,
-// each of 4 waves 64 x 128 (2 x 4 blocks).  Operands go from buffer loads
+// waves owns 64 x 64 (2 x 2 blocks of 32 x 32; up to 64 filters: the blocks in
+// use x 32), or, with the update fused, each of 4 waves 64 x 128 (2 x 4
+// blocks).  Operands go from buffer loads
 // straight into LDS as t-major rows (256 bytes of filters, 512 bytes of taps
 // per reduction index); one load instruction fills 1 KB, i.e. 4 (A) or 2 (B)
 // rows.  Rows are unpadded and XOR-swizzled: the 16-byte chunk c of row r sits
@@ -1021,12 +1022,15 @@ constexpr int WL_AT = WL_BK * WL_ARB, WL_BT = WL_BK * WL_BRB;
 constexpr int WL_STAGE = WL_AT + WL_BT;
 constexpr int WL_SMEM = 3 * WL_STAGE;  // 72 KB: two workgroups per CU
 
-template <bool NFAST, bool UPD, bool W8>
+template <bool NFAST, bool UPD, bool W8, int BLKS>
 __device__ __forceinline__ void wgrad_large_body(const WgradArgs& a) {
   constexpr uint32_t ES = 2;
-  // waves: 4 of 64 x 128 (2 x 4 blocks of 32 x 32), or with W8 8 of 64 x 64
+  // waves: 4 of 64 x 128 (2 x 4 blocks of 32 x 32), or with W8 8 of 64 x 64 or,
+  // with 1 or 2 (BLKS) of the tile's four 32-filter blocks in use, 8 of 32 BLKS x 32
   constexpr int NWV = W8 ? 8 : 4;
-  constexpr int FM = 2, FN = W8 ? 2 : 4;
+  constexpr bool ONE = BLKS < 4;  // one row of waves
+  static_assert(W8 || !ONE, "the update keeps the whole tile");
+  constexpr int FM = ONE ? BLKS : 2, FN = ONE ? 1 : W8 ? 2 : 4;
   constexpr int RPW = WL_BK / NWV;  // K-tile rows loaded by each wave (of A and of B)
   constexpr int AI = RPW / 4;       // A load instructions per wave (4 rows each)
   constexpr int BI = RPW / 2;       // B load instructions per wave (2 rows each)
@@ -1122,7 +1126,8 @@ __device__ __forceinline__ void wgrad_large_body(const WgradArgs& a) {
 
   // transpose-read addresses: lane -> column (lane & 31) of a 32-column block,
   // reduction rows 8 (lane / 32) + 0..7 of a 16-row step
-  const int wrow = W8 ? (wave >> 2) * 64 : (wave >> 1) * 64, wcol = W8 ? (wave & 3) * 64 : (wave & 1) * 128;
+  const int wrow = ONE ? 0 : W8 ? (wave >> 2) * 64 : (wave >> 1) * 64;
+  const int wcol = ONE ? wave * 32 : W8 ? (wave & 3) * 64 : (wave & 1) * 128;
   const int trow = 8 * (lane >> 5) + ((lane & 15) >> 2);
   const int low = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);  // chunk bits 0-1 within a 32-column block
   const int rr = (lane & 15) >> 2;                                // row & 3 (same for every step)
@@ -1382,9 +1387,24 @@ __device__ __forceinline__ void wgrad_large_body(const WgradArgs& a) {
 // for a third more fragment reads per MFMA (conv2 0.2512 -> 0.2293 ms,
 // conv4 0.1305 -> 0.1201, the others 1-3 %; bitwise the same results).  The
 // fused update keeps four waves.
-template <bool NFAST, bool UPD>
+// A layer of at most 64 filters uses half of the tile or less: its eight waves
+// stand side by side over the columns and read and multiply only the one or
+// two 32-filter blocks in use, instead of half of them working on zeros.  The
+// same sums in the same order (100 x 32 x 32 x 32 by 32 filters of 5 x 5:
+// 49.6 -> 42.0 us with the reduction; 64 x 112 x 112 x 64 by 64 of 3 x 3:
+// 167 -> 156; 250 x 27 x 27 x 96 by 24 of 3 x 3: 73 -> 58).  At 96 filters,
+// three of four blocks, the same layout was 2 % slower than 64 x 64.
+template <bool NFAST, bool UPD, int BLKS>
 __global__ __launch_bounds__(UPD ? NT : 2 * NT, 2) void conv_wgrad_large_kernel(WgradArgs a) {
-  wgrad_large_body<NFAST, UPD, !UPD>(a);
+  wgrad_large_body<NFAST, UPD, !UPD, BLKS>(a);
+}
+
+template <bool NFAST>
+void launch_wgrad_large(const WgradArgs& a, dim3 grid, hipStream_t st) {
+  if (a.update) hipLaunchKernelGGL((conv_wgrad_large_kernel<NFAST, true, 4>), grid, dim3(NT), 0, st, a);
+  else if (a.M > 64) hipLaunchKernelGGL((conv_wgrad_large_kernel<NFAST, false, 4>), grid, dim3(2 * NT), 0, st, a);
+  else if (a.M > 32) hipLaunchKernelGGL((conv_wgrad_large_kernel<NFAST, false, 2>), grid, dim3(2 * NT), 0, st, a);
+  else hipLaunchKernelGGL((conv_wgrad_large_kernel<NFAST, false, 1>), grid, dim3(2 * NT), 0, st, a);
 }
 
 // Filter-gradient split-K reduction over partial[split][M][Ng] (rows of ldp
@@ -1999,13 +2019,8 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
     static const char* names[2][2] = {{"conv_wgrad_large_kernel<0,0>", "conv_wgrad_large_kernel<0,1>"},
                                       {"conv_wgrad_large_kernel<1,0>", "conv_wgrad_large_kernel<1,1>"}};
     TraceScope ts(names[nf][a.update], st, flops, WORK_FLOP);
-    if (a.update) {
-      if (nf) hipLaunchKernelGGL((conv_wgrad_large_kernel<true, true>), grid, dim3(NT), 0, st, a);
-      else hipLaunchKernelGGL((conv_wgrad_large_kernel<false, true>), grid, dim3(NT), 0, st, a);
-    } else {
-      if (nf) hipLaunchKernelGGL((conv_wgrad_large_kernel<true, false>), grid, dim3(2 * NT), 0, st, a);
-      else hipLaunchKernelGGL((conv_wgrad_large_kernel<false, false>), grid, dim3(2 * NT), 0, st, a);
-    }
+    if (nf) launch_wgrad_large<true>(a, grid, st);
+    else launch_wgrad_large<false>(a, grid, st);
   } else if (tile) {
     plan.nfast = nf;
     const hipError_t e = launch_conv_wgrad_tile(a, plan, flops, st);

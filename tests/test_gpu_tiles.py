@@ -177,6 +177,34 @@ def test_f32_filter_gradient_least_workspace():
     assert rel_l2(db.cpu().numpy(), ref_db) <= TOL["f32"]
 
 
+# the bf16 filter gradient of few filters: one or two of a tile's four
+# 32-filter blocks in use, at their edges and one past; summed in one piece
+# and split, K-tiles of 32 images at one pixel (N = 32) and across pixels
+NARROW_CASES = [(32, 16, 6, 5, 8, 3, 3, 1, 1), (3, 40, 9, 7, 32, 1, 1, 0, 1), (5, 24, 11, 8, 40, 5, 5, 2, 1),
+                (32, 72, 4, 4, 64, 3, 3, 1, 1), (7, 8, 13, 13, 64, 3, 3, 0, 2), (1, 32, 3, 3, 24, 1, 1, 0, 1),
+                (1, 264, 4, 4, 56, 1, 1, 0, 1), (32, 16, 6, 5, 72, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("bias", [True, False], ids=["bias", "no-bias"])
+@pytest.mark.parametrize("case", NARROW_CASES, ids=["x".join(map(str, c)) for c in NARROW_CASES])
+def test_bf16_filter_gradient_of_few_filters(case, bias):
+    N, C, H, W, K, R, S, pad, stride = case
+    x, w, _ = _data(case, "bf16", 340)
+    P, Q = oracle.conv_out(H, R, pad, stride), oracle.conv_out(W, S, pad, stride)
+    dy = wl.random_array((N, K, P, Q), 343, "normal", 1.0, "bf16")
+    ref_dw, ref_db = oracle.conv_bwd_filter(x, dy, w.shape, pad=pad, stride=stride)
+    singa.trace_enable(True)
+    dw, db = singa.conv_bwd_filter(nchw_to_dev(x, "bf16"), nchw_to_dev(dy, "bf16"), (K, R, S, C), pad, stride,
+                                   with_bias=bias)
+    torch.cuda.synchronize()
+    names = [r[0] for r in singa.trace_records()]
+    singa.trace_enable(False)
+    assert any(n.startswith("conv_wgrad_large_kernel<") for n in names), names
+    assert rel_l2(dw.cpu().numpy().transpose(0, 3, 1, 2), ref_dw) <= TOL["bf16"]
+    if bias:
+        assert rel_l2(db.cpu().numpy(), ref_db) <= TOL["bf16"]
+
+
 # dense layers of one to three rows: the matrix-vector kernel, at widths
 # around its four columns a workgroup and reductions around the 256 chunks
 # that it takes at a time; four rows take a tile
