@@ -444,15 +444,17 @@ class Net:
         side_after = (self.side_update_layers[0]
                       if defer_join and self.side_update_layers and self.wgrad_stream is not None else None)
         self._issued = None
-        for i in range(len(self.layers) - 1, -1, -1):
-            g = self.layers[i].compute_gradient(g, need_dx=(i > 0 or need_input_grad))
-            if self.layers[i] is side_after:
-                # every backward-data pass that reads those layers' weights is issued
-                self._issued = torch.cuda.Event()
-                self._issued.record(self.main_stream)
-        if self.wgrad_stream is not None and self._issued is None:
-            self.main_stream.wait_stream(self.wgrad_stream)
-        self.main_stream = None
+        try:
+            for i in range(len(self.layers) - 1, -1, -1):
+                g = self.layers[i].compute_gradient(g, need_dx=(i > 0 or need_input_grad))
+                if self.layers[i] is side_after:
+                    # every backward-data pass that reads those layers' weights is issued
+                    self._issued = torch.cuda.Event()
+                    self._issued.record(self.main_stream)
+            if self.wgrad_stream is not None and self._issued is None:
+                self.main_stream.wait_stream(self.wgrad_stream)
+        finally:  # a pass that raised leaves no stream behind for a later layer call
+            self.main_stream = None
         return g
 
     def update(self):

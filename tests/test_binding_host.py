@@ -59,3 +59,21 @@ def test_another_stream_needs_its_buffers(missing):
     kw[missing] = None
     with pytest.raises(ValueError):
         singa.conv_bwd_filter(x, dy, (24, 3, 3, 16), 1, on=object(), **kw)
+
+
+def test_backward_that_raises_keeps_no_stream(monkeypatch):
+    """The stream looked up for a backward pass is not the one of a later
+    call when the pass ends in an exception."""
+    from paper_1603_07846_amd import net as gnet
+
+    class Broken:
+        def compute_gradient(self, g, need_dx):
+            raise RuntimeError("layer")
+
+    net = object.__new__(gnet.Net)
+    net.device, net.layers, net.side_update_layers = torch.device("cuda", 0), [Broken()], []
+    net.wgrad_stream = object()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: object())
+    with pytest.raises(RuntimeError, match="layer"):
+        net.backward()
+    assert net.main_stream is None
