@@ -233,6 +233,7 @@ struct FwdArgs {
   int tiles, tiles_n;
   float* partial;  // split-K: fp32 partial tiles [split][M][Nn] instead of y
   int kt_per_split;
+  int kt_per_piece;  // the tile kernel: K-tiles summed in one go; the sums of pieces are added in order
   const void* mask;  // optional [M][Nn] tensor: an output is zeroed where mask <= 0
   // 256-row kernel: K-tile kt covers channels [cs BK, cs BK + BK) of tap
   // rs = kt mod RS, cs = kt div RS (taps fastest), instead of taps [kt BK,
@@ -264,19 +265,30 @@ struct WgradArgs {
   int sh, sw, ph, pw;
   FastDiv dN, dPQ, dQ, dC, dS;
   int tiles, tiles_n, kt_per_split, nkt;
+  int kt_per_piece;  // as in FwdArgs
   int direct, acc_dw, acc_db;
   int update;    // direct only: each element is applied to `u` (out / db: NULL, or where g is also stored)
   SgdTargets u;
 };
 
+// K-tiles (of 32 terms) that an fp32 tile kernel sums in one go.  A rounding
+// error grows with the length of the running sum, so a split that is long
+// because the chip is full anyway would cost precision against the many short
+// ones of the 128 x 128 kernels; pieces of at most 256 terms do not, for 1 %
+// of the time (32 x 13 x 13 x 256, 384 filters of 3 x 3, forward and backward:
+// 291 -> 295 us; error against 64 bits 4.2e-7 -> 2.1e-7, 3.1e-7 with the 128 x
+// 128 kernels).
+constexpr int F32_PIECE = 8;
+
 // Tile and reduction splits of the fp32 tile kernel (conv_wgrad_tile.hip).
 struct WgradTilePlan {
   int tile;    // index into the kernel's table of tiles
   int splits;  // > 1: partial tiles in WgradArgs::out
+  int pieces;  // of the reduction, each summed in one go, the sums added in order (at least one to a split)
   bool nfast;  // a K-tile is 32 images at one output pixel
 };
 // max_splits: what the caller's workspace has room for.
-WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits);
+WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits, int pieces);
 int wgrad_tile_rows(int tile);
 hipError_t launch_conv_wgrad_tile(WgradArgs a, const WgradTilePlan& p, double flops, hipStream_t st);
 
@@ -286,9 +298,9 @@ hipError_t launch_conv_wgrad_tile(WgradArgs a, const WgradTilePlan& p, double fl
 struct FwdTilePlan {
   int tile;    // index into the kernel's table of tiles
   int segs;    // pieces of the tap range, summed one by one and added in order
-  int splits;  // 1: a workgroup runs all pieces; segs: one each, fp32 partial tiles [split][M][Nn] in FwdArgs::partial
+  int splits;  // workgroups over the taps (bf16: 1 or segs); > 1: fp32 partial tiles [split][M][Nn] in FwdArgs::partial
 };
-// segs: the pieces a bf16 GEMM's tap range is summed in (fp32 chooses its own).
+// segs: the pieces the tap range is summed in (fp32: at least).
 FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs);
 hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd, double flops, hipStream_t st);
 // A dense layer (P = Q = 1 and the window covers the whole input) of at most

@@ -44,7 +44,7 @@ constexpr int kTileWaves[TILES] = {8, 8, 4, 4, 4, 4, 4, 4, 4};
 template <int ID>
 constexpr int kWorkgroupsPerCu = TileDef<ID>::NS * (TileDef<ID>::BM + TileDef<ID>::BN) * RB * 2 <= 163840 ? 2 : 1;
 
-// SEG: the workgroup runs several pieces of the tap range (kt_per_split K-tiles
+// SEG: the workgroup runs several pieces of the tap range (kt_per_piece K-tiles
 // each) and adds their sums in order, as the reduction of a split GEMM does.
 template <typename T, int ID, bool SEG>
 __global__ __launch_bounds__(64 * TileDef<ID>::NW, kWorkgroupsPerCu<ID>) void conv_fwd_tile_kernel(FwdArgs a) {
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * TileDef<ID>::NW, kWorkgroupsPerCu<ID>) void co
 
   const int nkt_all = (a.Kg + LBK - 1) / LBK;
   const int kt0 = split * a.kt_per_split;
-  const int nkt = SEG ? nkt_all : min(a.kt_per_split, nkt_all - kt0);  // K-tiles of this workgroup (>= 1)
+  const int nkt = min(a.kt_per_split, nkt_all - kt0);  // K-tiles of this workgroup (>= 1)
 
   // The taps of K-tile kt: where the lane's chunks start in the filter row
   // and in the input window.  With whole K-tiles per tap (a.uni) tap and
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * TileDef<ID>::NW, kWorkgroupsPerCu<ID>) void co
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = sum[i][j][v] = 0.f;
-  int left = a.kt_per_split;  // SEG: K-tiles of the current piece still to run
+  int left = a.kt_per_piece;  // SEG: K-tiles of the current piece still to run
 
   const int wm = wave / WC, wn = wave % WC;
   const int li = lane & 31, lh = lane >> 5;
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * TileDef<ID>::NW, kWorkgroupsPerCu<ID>) void co
     }
     stage = stage == NS - 1 ? 0 : stage + 1;
     if (SEG && (--left == 0 || kt + 1 == nkt)) {
-      left = a.kt_per_split;
+      left = a.kt_per_piece;
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -288,12 +288,9 @@ constexpr const char* kTileNames[2][2][TILES] = {{TILE_NAMES("f32", 0), TILE_NAM
 #undef TILE_NAMES
 #undef TILE_NAME
 
-
-
-
 template <typename T, int ID> void launch_tile(const FwdArgs& a, const FwdTilePlan& p, hipStream_t st) {
   const dim3 grid(a.tiles * p.splits), block(64 * TileDef<ID>::NW);
-  if (p.segs > p.splits) hipLaunchKernelGGL((conv_fwd_tile_kernel<T, ID, true>), grid, block, 0, st, a);
+  if (a.kt_per_piece < a.kt_per_split) hipLaunchKernelGGL((conv_fwd_tile_kernel<T, ID, true>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((conv_fwd_tile_kernel<T, ID, false>), grid, block, 0, st, a);
 }
 
@@ -418,13 +415,16 @@ template <typename T> void launch_gemv(const FwdArgs& a, hipStream_t st) {
 // average 2 % slower than the best one timed, 14 % at worst.
 // A bf16 GEMM's sum is taken in `segs` pieces whatever the tile, so that its
 // results do not depend on the choice; its workgroups run all of them or one
-// each.  An fp32 GEMM takes the split count that the model likes best.
+// each.  An fp32 GEMM takes the split count that the model likes best; where
+// that makes a workgroup's share of the taps longer than a piece, the
+// workgroup sums it piece by piece (F32_PIECE).
 FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs) {
   const int lbk = RB / (int)dt_size(dt);
   const int nkt = (int)((Kg + lbk - 1) / lbk);
+  if (dt != BF16) segs = std::max(segs, (nkt + F32_PIECE - 1) / F32_PIECE);
   if (const char* e = tuning_env("SINGA_FWD_TILE")) {
     int t = 0, s = 1;
-    if (sscanf(e, "%d,%d", &t, &s) == 2) return FwdTilePlan{t, dt == BF16 ? segs : s, dt == BF16 && s > 1 ? segs : s};
+    if (sscanf(e, "%d,%d", &t, &s) == 2) return FwdTilePlan{t, segs, dt == BF16 && s > 1 ? segs : s};
   }
   struct Model {
     float one0, one_area, one_edge;  // K-tile step of a workgroup alone on its CU
@@ -478,7 +478,7 @@ FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs) {
       if (splits[i] > 1) us += m.red0 + (m.red_split + m.red_mb * mb) * splits[i];
       if (us < best_us) {
         best_us = us;
-        best = FwdTilePlan{t, dt == BF16 ? segs : splits[i], splits[i]};
+        best = FwdTilePlan{t, segs, splits[i]};
       }
     }
   }
@@ -490,7 +490,8 @@ hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd
   a.tiles_n = (a.Nn + kTileCols[p.tile] - 1) / kTileCols[p.tile];
   a.tiles = (a.M + kTileRows[p.tile] - 1) / kTileRows[p.tile] * a.tiles_n;
   const int nkt = (a.Kg + lbk - 1) / lbk;
-  a.kt_per_split = (nkt + p.segs - 1) / p.segs;
+  a.kt_per_split = (nkt + p.splits - 1) / p.splits;
+  a.kt_per_piece = (nkt + p.segs - 1) / p.segs;
   // bf16: the taps in the filter row's order; fp32: taps fastest, so that
   // consecutive K-tiles read the same channels one tap apart and their
   // overlapping input rows meet in the caches

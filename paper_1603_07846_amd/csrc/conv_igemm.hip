@@ -1952,9 +1952,10 @@ WgradChoice wgrad_choose(const ConvShape& s, int dt, bool va, int vb, size_t par
   const long Ng = (long)s.R * s.S * s.C + (bias ? 1 : 0);
   if (c.tile) {
     const long max_splits = (long)(partial_bytes / ((size_t)s.K * ((Ng + 63) / 64 * 64) * sizeof(float)));
-    c.plan = wgrad_tile_plan(s.K, Ng, (long)s.N * s.P * s.Q, max_splits);
+    // pieces: no fewer than the splits of the 128 x 128 kernel
+    c.plan = wgrad_tile_plan(s.K, Ng, (long)s.N * s.P * s.Q, max_splits, wgrad_splits_for(s, dt, bias, false));
   } else {
-    c.plan = WgradTilePlan{0, wgrad_splits_for(s, dt, bias, c.large), false};
+    c.plan = WgradTilePlan{0, wgrad_splits_for(s, dt, bias, c.large), 1, false};
   }
   return c;
 }
@@ -2081,7 +2082,7 @@ size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least) {
   int splits = wgrad_splits_for(s, dt, bias, false);
   if (wgrad_large_shape(s, dt)) splits = std::max(splits, wgrad_splits_for(s, dt, bias, true));
   if (!least && dt == F32 && s.K % 4 == 0 && s.C % 4 == 0)
-    splits = std::max(splits, wgrad_tile_plan(s.K, (long)Ng, (long)s.N * s.P * s.Q, LONG_MAX).splits);
+    splits = std::max(splits, wgrad_tile_plan(s.K, (long)Ng, (long)s.N * s.P * s.Q, LONG_MAX, 1).splits);
   return splits > 1 ? (size_t)splits * s.K * ldp * sizeof(float) : 0;
 }
 

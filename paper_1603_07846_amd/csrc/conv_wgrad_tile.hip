@@ -27,7 +27,10 @@ constexpr int WBN = 128, WBK = 32;
 
 // NFAST: N % 32 == 0 and few output pixels: a K-tile holds 32 images at one
 // output pixel; otherwise the reduction runs image by image.
-template <int ID, bool NFAST>
+// SEG: the workgroup sums pieces of kt_per_piece K-tiles and adds their sums
+// in order, so that a few long splits lose no precision against many short
+// ones.
+template <int ID, bool NFAST, bool SEG>
 __global__ __launch_bounds__(NT, 2) void conv_wgrad_tile_kernel(WgradArgs a) {
   typedef WTile<ID> D;
   constexpr int BMT = D::BM, NS = D::NS, WR = D::WR, WC = 4 / WR;
@@ -105,13 +108,14 @@ __global__ __launch_bounds__(NT, 2) void conv_wgrad_tile_kernel(WgradArgs a) {
     }
   };
 
-  f32x16 acc[FM][FN];
+  f32x16 acc[FM][FN], sum[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = sum[i][j][v] = 0.f;
+  int left = a.kt_per_piece;  // SEG: K-tiles of the current piece still to run
 
   // fragment of the 2-row step kc: lane -> column (lane & 31) of a 32-column
   // block, row 2 kc + lane / 32
@@ -159,6 +163,24 @@ __global__ __launch_bounds__(NT, 2) void conv_wgrad_tile_kernel(WgradArgs a) {
           acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[bm], fb[bn], acc[bm][bn], 0, 0, 0);
     }
     stage = stage == NS - 1 ? 0 : stage + 1;
+    if (SEG && (--left == 0 || k + 1 == nk)) {
+      left = a.kt_per_piece;
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            sum[i][j][v] += acc[i][j][v];
+            acc[i][j][v] = 0.f;
+          }
+    }
+  }
+  if constexpr (SEG) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = sum[i][j];
   }
   wait_vmcnt<0>();  // the trailing all-OOB loads still write LDS
 
@@ -192,8 +214,11 @@ constexpr const char* kWNames[WTILES][2] = {
 
 template <int ID> void launch_wtile(const WgradArgs& a, const WgradTilePlan& p, hipStream_t st) {
   const dim3 grid(a.tiles * p.splits);
-  if (p.nfast) hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, true>), grid, dim3(NT), 0, st, a);
-  else hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, false>), grid, dim3(NT), 0, st, a);
+  const bool seg = a.kt_per_piece < a.kt_per_split;
+  if (p.nfast && seg) hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, true, true>), grid, dim3(NT), 0, st, a);
+  else if (p.nfast) hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, true, false>), grid, dim3(NT), 0, st, a);
+  else if (seg) hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, false, true>), grid, dim3(NT), 0, st, a);
+  else hipLaunchKernelGGL((conv_wgrad_tile_kernel<ID, false, false>), grid, dim3(NT), 0, st, a);
 }
 
 }  // namespace
@@ -206,17 +231,18 @@ int wgrad_tile_rows(int tile) { return kWRows[tile]; }
 // constants are a least-squares fit to some 600 timed launches over 24 layers
 // (filters 12 - 4,096, taps 5 - 5,185, reductions of 10 - 137,904); over these
 // the choice is on average 1 % slower than the best one timed, 8 % at worst.
-WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits) {
+WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits, int pieces) {
   const int nkt = (int)((T + WBK - 1) / WBK);
+  pieces = std::max(pieces, (nkt + F32_PIECE - 1) / F32_PIECE);
   if (const char* e = tuning_env("SINGA_WGRAD_TILE")) {
     int t = 0, s = 1;
     if (sscanf(e, "%d,%d", &t, &s) == 2) {
       const int per = (nkt + s - 1) / s;
-      return WgradTilePlan{t, (nkt + per - 1) / per, false};
+      return WgradTilePlan{t, (nkt + per - 1) / per, pieces, false};
     }
   }
   const float mb = 1e-6f * (float)M * (float)((Ng + 63) / 64 * 64);
-  WgradTilePlan best{0, 1, false};
+  WgradTilePlan best{0, 1, pieces, false};
   float best_us = 1e30f;
   for (int want : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
     if (want > 1 && nkt < 2 * want) break;
@@ -232,7 +258,7 @@ WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits) {
       if (splits > 1) us += 4.37f + 0.00216f * splits + 0.735f * mb * splits;
       if (us < best_us) {
         best_us = us;
-        best = WgradTilePlan{t, splits, false};
+        best = WgradTilePlan{t, splits, pieces, false};
       }
     }
   }
@@ -240,6 +266,7 @@ WgradTilePlan wgrad_tile_plan(long M, long Ng, long T, long max_splits) {
 }
 
 hipError_t launch_conv_wgrad_tile(WgradArgs a, const WgradTilePlan& p, double flops, hipStream_t st) {
+  a.kt_per_piece = (a.nkt + p.pieces - 1) / p.pieces;
   TraceScope ts(kWNames[p.tile][p.nfast], st, flops, WORK_FLOP);
   switch (p.tile) {
     case 0: launch_wtile<0>(a, p, st); break;
