@@ -110,7 +110,9 @@ int singa_conv_out_shape(const singa_shape4* x, const singa_filter4* w,
  * Errors: NULL, SHAPE, UNSUPPORTED (window larger than 255 cells, pad >= window). */
 int singa_pool_out_shape(const singa_shape4* x, const singa_pool_desc* d, singa_shape4* y);
 
-/* Workspace bytes that `op` needs for this problem (0 when none).  Host-only.
+/* Workspace bytes that `op` needs for this problem (0 when none), with a bias
+ * or without (the form without can need more: a filter gradient of one column
+ * less may be cut into more partial sums).  Host-only.
  * Errors: NULL, SHAPE, UNSUPPORTED. */
 int singa_conv_workspace_bytes(int op, singa_dtype dtype, singa_layout layout,
                                const singa_shape4* x, const singa_filter4* w,

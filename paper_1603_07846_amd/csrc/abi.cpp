@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cstdint>
 
@@ -350,10 +351,18 @@ int singa_conv_workspace_bytes(int op, singa_dtype dtype, singa_layout layout, c
   switch (op) {
     case SINGA_OP_FWD: { FwdWs o; *bytes = carve_fwd(s, dtype, layout, nullptr, &o); break; }
     case SINGA_OP_BWD_DATA: { BwdDataWs o; *bytes = carve_bwd_data(s, dtype, layout, nullptr, &o); break; }
-    case SINGA_OP_BWD_FILTER: { BwdFilterWs o; *bytes = carve_bwd_filter(s, dtype, layout, true, nullptr, &o); break; }
+    // the larger of the two forms of the call: one column less, without the
+    // bias, can take more splits and more workspace
+    case SINGA_OP_BWD_FILTER: {
+      BwdFilterWs o;
+      *bytes = std::max(carve_bwd_filter(s, dtype, layout, true, nullptr, &o),
+                        carve_bwd_filter(s, dtype, layout, false, nullptr, &o));
+      break;
+    }
     case SINGA_OP_BWD_FILTER_SGD: {
       BwdFilterSgdWs o;
-      *bytes = carve_bwd_filter_sgd(s, dtype, layout, true, nullptr, &o);
+      *bytes = std::max(carve_bwd_filter_sgd(s, dtype, layout, true, nullptr, &o),
+                        carve_bwd_filter_sgd(s, dtype, layout, false, nullptr, &o));
       break;
     }
     default: return SINGA_ERR_UNSUPPORTED;

@@ -1933,6 +1933,10 @@ int wgrad_splits_for(const ConvShape& s, int dt, bool bias, bool large) {
     }();
     const long nkt = (T + WL_BK - 1) / WL_BK;
     const long target = forced ? forced : tiles <= 4 ? 640 : 448;
+    // one split with a bias column (never more tiles without): one without
+    // it too, so that the update is fused into both forms or into neither,
+    // as the workspace query, which is not told of the bias, reports
+    if (!bias && wgrad_splits_for(s, dt, true, true) == 1) return 1;
     return wgrad_split_count(tiles, nkt, target);
   }
   const long tiles = ((M + BM - 1) / BM) * ((Ng + BN - 1) / BN);
