@@ -42,8 +42,9 @@
  *     threads at once; the only process-wide state is the optional timing
  *     trace (singa_trace_*), a switch the caller sets.  Concurrent calls on
  *     different streams must not share output or workspace buffers.  The
- *     dispatch rules (tile layouts, split counts) depend on the shapes only,
- *     never on the environment.
+ *     dispatch rules (tile layouts, split counts) depend on the shapes, the
+ *     pointers' alignment and, in fp32, on whether the workspace has the
+ *     reported size (see singa_conv_workspace_bytes), never on the environment.
  */
 #ifndef SINGA_MI_H
 #define SINGA_MI_H
@@ -60,7 +61,7 @@ extern "C" {
 #define SINGA_ERR_NULL (-1)        /* a required pointer argument is NULL */
 #define SINGA_ERR_SHAPE (-2)       /* non-positive or inconsistent sizes, empty output */
 #define SINGA_ERR_UNSUPPORTED (-3) /* dtype/layout/parameter combination not provided */
-#define SINGA_ERR_WORKSPACE (-4)   /* workspace smaller than singa_conv_workspace_bytes() */
+#define SINGA_ERR_WORKSPACE (-4)   /* workspace too small (singa_conv_workspace_bytes() is always enough) */
 #define SINGA_ERR_ALIGN (-5)       /* a device pointer is misaligned (see below) */
 #define SINGA_ERR_HIP (-6)         /* the HIP runtime rejected a launch */
 #define SINGA_ERR_SCRATCH (-7)     /* needs more than the library's fixed scratch array holds */
@@ -112,7 +113,10 @@ int singa_pool_out_shape(const singa_shape4* x, const singa_pool_desc* d, singa_
 
 /* Workspace bytes that `op` needs for this problem (0 when none), with a bias
  * or without (the form without can need more: a filter gradient of one column
- * less may be cut into more partial sums).  Host-only.
+ * less may be cut into more partial sums).  An fp32 call takes up to 64 MiB
+ * of this for more partial sums than it has to make; with a workspace that is
+ * too small for those it makes fewer (the results then differ in rounding),
+ * down to SINGA_ERR_WORKSPACE.  Host-only.
  * Errors: NULL, SHAPE, UNSUPPORTED. */
 int singa_conv_workspace_bytes(int op, singa_dtype dtype, singa_layout layout,
                                const singa_shape4* x, const singa_filter4* w,
@@ -202,8 +206,9 @@ int singa_conv_bwd_filter(singa_dtype dtype, singa_layout layout,
  * here or later).
  *   Returns SINGA_ERR_SCRATCH (nothing enqueued) when the call would need
  *   more than SINGA_NOALLOC_SCRATCH_BYTES of workspace
- *   (singa_conv_workspace_bytes(SINGA_OP_BWD_FILTER, ...) reports it; every
- *   AlexNet-shaped layer up to batch 256 fits), and SINGA_ERR_UNSUPPORTED
+ *   (singa_conv_workspace_bytes(SINGA_OP_BWD_FILTER, ...) reports the larger
+ *   of the calls with and without db; every AlexNet-shaped layer up to batch
+ *   256 fits), and SINGA_ERR_UNSUPPORTED
  *   when `stream` belongs to another device than the current one.
  *   Every call on one GPU uses that GPU's one array: calls whose execution
  *   overlaps on the same GPU (different streams, or several host threads)

@@ -162,11 +162,14 @@ bool s2d_input_ok(const ConvShape& s, int dt) {
 
 // One function computes both the size and the layout of every workspace, so
 // the two can never disagree.
-struct FwdWs { void *x, *w, *y, *xp, *wp; float* partial; };
-struct BwdDataWs { void *dy, *w, *wt, *dx, *ws, *dxs; float* partial; };
+// least: the smallest size that works.  fp32 GEMMs make more partial sums than
+// that where the time model says so; a workspace that does not hold them all
+// serves with as many splits as the smallest size has room for.
+struct FwdWs { void *x, *w, *y, *xp, *wp; float* partial; size_t partial_bytes; };
+struct BwdDataWs { void *dy, *w, *wt, *dx, *ws, *dxs; float* partial; size_t partial_bytes; };
 struct BwdFilterWs { void *x, *dy, *xp; float *dw, *dwp, *partial; size_t partial_bytes; };
 
-size_t carve_fwd(const ConvShape& s, int dt, int layout, void* ws, FwdWs* o) {
+size_t carve_fwd(const ConvShape& s, int dt, int layout, void* ws, FwdWs* o, bool least = false) {
   Carve c(ws);
   o->x = o->w = o->y = o->xp = o->wp = nullptr;
   o->partial = nullptr;
@@ -181,8 +184,8 @@ size_t carve_fwd(const ConvShape& s, int dt, int layout, void* ws, FwdWs* o) {
     if (layout != SINGA_NHWC_S2D) o->xp = c.take((size_t)g.N * g.H * g.W * g.C * dt_size(dt));
     o->wp = c.take((size_t)g.K * g.R * g.S * g.C * dt_size(dt));
   }
-  const size_t pb = fwd_partial_bytes(g, dt);
-  if (pb) o->partial = (float*)c.take(pb);
+  o->partial_bytes = fwd_partial_bytes(g, dt, least);
+  if (o->partial_bytes) o->partial = (float*)c.take(o->partial_bytes);
   return c.used;
 }
 
@@ -192,7 +195,8 @@ hipError_t conv_fwd_nhwc(int dt, const ConvShape& s, const void* x, const void* 
                          int relu, const FwdWs& o, hipStream_t st, bool x_s2d = false) {
   ConvShape g;
   const Rewrite rw = input_rewrite(s, dt, &g);
-  if (rw == RW_NONE) return launch_conv_fwd(dt, s, x, w, bias, y, relu, 0, conv_flops(s), o.partial, nullptr, st);
+  if (rw == RW_NONE)
+    return launch_conv_fwd(dt, s, x, w, bias, y, relu, 0, conv_flops(s), o.partial, o.partial_bytes, nullptr, st);
   hipError_t e;
   if (rw == RW_PAD) {
     e = launch_pad_channels(dt, x, o.xp, (long)s.N * s.H * s.W, w, o.wp, (long)s.K * s.R * s.S, s.C, g.C, st);
@@ -201,14 +205,16 @@ hipError_t conv_fwd_nhwc(int dt, const ConvShape& s, const void* x, const void* 
     if (e == hipSuccess) e = launch_filter_to_s2d(dt, s, g, w, o.wp, st);
   }
   if (e == hipSuccess)
-    e = launch_conv_fwd(dt, g, x_s2d ? x : o.xp, o.wp, bias, y, relu, 0, conv_flops(s), o.partial, nullptr, st);
+    e = launch_conv_fwd(dt, g, x_s2d ? x : o.xp, o.wp, bias, y, relu, 0, conv_flops(s), o.partial, o.partial_bytes,
+                        nullptr, st);
   return e;
 }
 
-size_t carve_bwd_data(const ConvShape& s, int dt, int layout, void* ws, BwdDataWs* o) {
+size_t carve_bwd_data(const ConvShape& s, int dt, int layout, void* ws, BwdDataWs* o, bool least = false) {
   Carve c(ws);
   o->dy = o->w = o->wt = o->dx = o->ws = o->dxs = nullptr;
   o->partial = nullptr;
+  o->partial_bytes = 0;
   if (layout == SINGA_NCHW) {
     o->dy = c.take(out_bytes(s, dt));
     o->w = c.take(filt_bytes(s, dt));
@@ -217,15 +223,14 @@ size_t carve_bwd_data(const ConvShape& s, int dt, int layout, void* ws, BwdDataW
   ConvShape g;
   if (bwd_data_gemm(s)) {
     o->wt = c.take(filt_bytes(s, dt));
-    const size_t pb = fwd_partial_bytes(bwd_data_inner(s), dt);
-    if (pb) o->partial = (float*)c.take(pb);
+    o->partial_bytes = fwd_partial_bytes(bwd_data_inner(s), dt, least);
   } else if (bwd_data_s2d(s, &g)) {
     o->ws = c.take(filt_bytes(g, dt));
     o->wt = c.take(filt_bytes(g, dt));
     o->dxs = c.take(act_bytes(g, dt));
-    const size_t pb = fwd_partial_bytes(bwd_data_inner(g), dt);
-    if (pb) o->partial = (float*)c.take(pb);
+    o->partial_bytes = fwd_partial_bytes(bwd_data_inner(g), dt, least);
   }
+  if (o->partial_bytes) o->partial = (float*)c.take(o->partial_bytes);
   return c.used;
 }
 
@@ -240,11 +245,18 @@ size_t carve_bwd_filter(const ConvShape& s, int dt, int layout, bool bias, void*
     o->dw = (float*)c.take((size_t)s.K * s.R * s.S * s.C * sizeof(float));
   }
   ConvShape g;
+  size_t given = 0;  // an input given in the space-to-depth layout counts as if it were made here
   if (input_rewrite(s, dt, &g) != RW_NONE) {
-    if (layout != SINGA_NHWC_S2D) o->xp = c.take((size_t)g.N * g.H * g.W * g.C * dt_size(dt));
+    const size_t xb = (size_t)g.N * g.H * g.W * g.C * dt_size(dt);
+    if (layout != SINGA_NHWC_S2D) o->xp = c.take(xb);
+    else given = align_up(xb);
     o->dwp = (float*)c.take((size_t)g.K * g.R * g.S * g.C * sizeof(float));
   }
-  o->partial_bytes = wgrad_partial_bytes(g, dt, bias, least);
+  // More partial sums than the least only where all of it fits the fixed
+  // scratch array: the allocation-free call makes the same splits.
+  const size_t other = c.used + given, scratch = SINGA_NOALLOC_SCRATCH_BYTES;
+  const size_t room = least || other >= scratch ? 0 : std::min(PARTIAL_ROOM, scratch - other);
+  o->partial_bytes = wgrad_partial_bytes(g, dt, bias, room);
   o->partial = o->partial_bytes ? (float*)c.take(o->partial_bytes) : nullptr;
   return c.used;
 }
@@ -258,6 +270,7 @@ struct BwdFilterSgdWs {
   float* gb;
   void* inner;
   size_t inner_bytes;
+  bool least;  // of the inner one
 };
 
 bool bwd_filter_sgd_fused(const ConvShape& s, int dt, int layout, bool bias) {
@@ -265,19 +278,32 @@ bool bwd_filter_sgd_fused(const ConvShape& s, int dt, int layout, bool bias) {
   return layout == SINGA_NHWC && input_rewrite(s, dt, &g) == RW_NONE && wgrad_update_fusable(s, dt, bias);
 }
 
-size_t carve_bwd_filter_sgd(const ConvShape& s, int dt, int layout, bool bias, void* ws, BwdFilterSgdWs* o) {
+size_t carve_bwd_filter_sgd(const ConvShape& s, int dt, int layout, bool bias, void* ws, BwdFilterSgdWs* o,
+                            bool least = false) {
   Carve c(ws);
   o->fused = bwd_filter_sgd_fused(s, dt, layout, bias);
   o->g = o->gb = nullptr;
   o->inner = nullptr;
   o->inner_bytes = 0;
+  o->least = least;
   if (o->fused) return 0;
   o->g = (float*)c.take((size_t)s.K * s.R * s.S * s.C * sizeof(float));
   if (bias) o->gb = (float*)c.take((size_t)s.K * sizeof(float));
   BwdFilterWs f;
-  o->inner_bytes = carve_bwd_filter(s, dt, layout, bias, nullptr, &f);
+  o->inner_bytes = carve_bwd_filter(s, dt, layout, bias, nullptr, &f, least);
   o->inner = o->inner_bytes ? c.take(o->inner_bytes) : nullptr;
   return c.used;
+}
+
+// Carves the caller's workspace: as the query reports it or, where that does
+// not fit, the smallest size that works.  carve(ws, least) returns its size.
+template <typename F> int take_workspace(void* ws, size_t ws_bytes, F carve) {
+  size_t need = carve(nullptr, false);
+  const bool least = need > 0 && (!ws || ws_bytes < need);
+  if (least) need = carve(nullptr, true);
+  if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
+  carve(ws, least);
+  return SINGA_OK;
 }
 
 // Filter KCRS (NCHW callers) -> KRSC.
@@ -287,6 +313,18 @@ hipError_t kcrs_to_krsc(int dt, const ConvShape& s, const void* in, void* out, h
 }
 
 }  // namespace
+
+int singa::conv_bwd_filter_bytes(int dtype, int layout, const singa_shape4* x, const singa_filter4* w,
+                                 const singa_conv_desc* d, bool bias, size_t* bytes) {
+  if (!dtype_ok(dtype) || !(layout_ok(layout) || layout == SINGA_NHWC_S2D)) return SINGA_ERR_UNSUPPORTED;
+  ConvShape s;
+  const int rc = conv_geometry(x, w, d, &s);
+  if (rc != SINGA_OK) return rc;
+  if (layout == SINGA_NHWC_S2D && !s2d_input_ok(s, dtype)) return SINGA_ERR_UNSUPPORTED;
+  BwdFilterWs o;
+  *bytes = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o);
+  return SINGA_OK;
+}
 
 extern "C" {
 
@@ -409,9 +447,8 @@ int singa_conv_fwd(singa_dtype dtype, singa_layout layout, const singa_shape4* x
       !aligned_to(ws, 16))
     return SINGA_ERR_ALIGN;
   FwdWs o;
-  const size_t need = carve_fwd(s, dtype, layout, nullptr, &o);
-  if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
-  carve_fwd(s, dtype, layout, ws, &o);
+  rc = take_workspace(ws, ws_bytes, [&](void* p, bool least) { return carve_fwd(s, dtype, layout, p, &o, least); });
+  if (rc != SINGA_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (layout != SINGA_NCHW)
     return hip_status(conv_fwd_nhwc(dtype, s, x_ptr, w_ptr, bias, y_ptr, fuse_relu, o, st, layout == SINGA_NHWC_S2D));
@@ -438,9 +475,9 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
   if (relu_y && layout == SINGA_NCHW && (!aligned_to(relu_y, 16) || !aligned_to(dx_ptr, 16)))
     return SINGA_ERR_ALIGN;
   BwdDataWs o;
-  const size_t need = carve_bwd_data(s, dtype, layout, nullptr, &o);
-  if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
-  carve_bwd_data(s, dtype, layout, ws, &o);
+  rc = take_workspace(ws, ws_bytes,
+                      [&](void* p, bool least) { return carve_bwd_data(s, dtype, layout, p, &o, least); });
+  if (rc != SINGA_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const void* dy = dy_ptr;
@@ -466,12 +503,12 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
         e = launch_transpose(dtype, o.ws, o.wt, RSg, g.K, g.C, g.C, (long)RSg * g.C, g.K, (long)RSg * g.K, 1, st);
       if (e == hipSuccess)
         e = launch_conv_fwd(dtype, bwd_data_inner(g), dy, o.wt, nullptr, o.dxs, 0, 1, conv_flops(s), o.partial,
-                            nullptr, st);
+                            o.partial_bytes, nullptr, st);
       if (e == hipSuccess) e = launch_depth_to_space(dtype, s, g, o.dxs, nhwc_mask, dx, st);
     } else if (bwd_data_gemm(s)) {
       // dense geometry: the GEMM reads w itself as the transposed filter when it can
       e = bwd_data_fc(s) ? launch_conv_fwd_wt(dtype, bwd_data_inner(s), dy, wk, dx, 1, conv_flops(s), o.partial,
-                                              nhwc_mask, st)
+                                              o.partial_bytes, nhwc_mask, st)
                          : hipErrorNotSupported;
       if (e == hipErrorNotSupported) {
         if (bwd_data_fc(s)) {
@@ -484,7 +521,7 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
         }
         if (e == hipSuccess)
           e = launch_conv_fwd(dtype, bwd_data_inner(s), dy, o.wt, nullptr, dx, 0, 1, conv_flops(s), o.partial,
-                              nhwc_mask, st);
+                              o.partial_bytes, nhwc_mask, st);
       }
     } else {
       e = launch_conv_bwd_data_direct(dtype, s, dy, wk, dx, nhwc_mask, st);
@@ -510,13 +547,9 @@ int singa_conv_bwd_filter(singa_dtype dtype, singa_layout layout, const singa_sh
     return SINGA_ERR_ALIGN;
   BwdFilterWs o;
   const bool bias = db != nullptr;
-  // a workspace that holds only the least number of partial tiles (the fixed
-  // scratch array's limit) still serves, with fewer splits
-  size_t need = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o);
-  const bool least = ws_bytes < need;
-  if (least) need = carve_bwd_filter(s, dtype, layout, bias, nullptr, &o, true);
-  if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
-  carve_bwd_filter(s, dtype, layout, bias, ws, &o, least);
+  rc = take_workspace(ws, ws_bytes,
+                      [&](void* p, bool least) { return carve_bwd_filter(s, dtype, layout, bias, p, &o, least); });
+  if (rc != SINGA_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const void* xx = x_ptr;
@@ -573,9 +606,10 @@ int singa_conv_bwd_filter_sgd(singa_dtype dtype, singa_layout layout, const sing
     return SINGA_ERR_ALIGN;
   const bool bias = b_master != nullptr;
   BwdFilterSgdWs o;
-  const size_t need = carve_bwd_filter_sgd(s, dtype, layout, bias, nullptr, &o);
-  if (need > 0 && (!ws || ws_bytes < need)) return SINGA_ERR_WORKSPACE;
-  carve_bwd_filter_sgd(s, dtype, layout, bias, ws, &o);
+  rc = take_workspace(ws, ws_bytes, [&](void* p, bool least) {
+    return carve_bwd_filter_sgd(s, dtype, layout, bias, p, &o, least);
+  });
+  if (rc != SINGA_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (o.fused) {
     if (!aligned_to(x_ptr, 16) || !aligned_to(dy_ptr, 16)) return SINGA_ERR_ALIGN;
@@ -587,9 +621,10 @@ int singa_conv_bwd_filter_sgd(singa_dtype dtype, singa_layout layout, const sing
   ConvShape g0;
   if (layout == SINGA_NHWC && input_rewrite(s, dtype, &g0) == RW_NONE) {
     BwdFilterWs f;
-    carve_bwd_filter(s, dtype, layout, bias, o.inner, &f);
+    carve_bwd_filter(s, dtype, layout, bias, o.inner, &f, o.least);
     const SgdTargets u{w_master, w_mom, w_bf16, b_master, b_mom, b_bf16, lr, momentum, weight_decay};
-    const hipError_t e = launch_conv_wgrad_reduce_sgd(dtype, s, x_ptr, dy_ptr, f.partial, dw, db, u, conv_flops(s), st);
+    const hipError_t e = launch_conv_wgrad_reduce_sgd(dtype, s, x_ptr, dy_ptr, f.partial, f.partial_bytes, dw, db, u,
+                                                      conv_flops(s), st);
     if (e != hipErrorNotSupported) return hip_status(e);
   }
   float* g = dw ? dw : o.g;

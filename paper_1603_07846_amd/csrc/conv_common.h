@@ -300,8 +300,9 @@ struct FwdTilePlan {
   int segs;    // pieces of the tap range, summed one by one and added in order
   int splits;  // workgroups over the taps (bf16: 1 or segs); > 1: fp32 partial tiles [split][M][Nn] in FwdArgs::partial
 };
-// segs: the pieces the tap range is summed in (fp32: at least).
-FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs);
+// segs: the pieces the tap range is summed in (fp32: at least); max_splits:
+// what the workspace has room for (fp32; bf16 takes segs partial sums or none).
+FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs, long max_splits);
 hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd, double flops, hipStream_t st);
 // A dense layer (P = Q = 1 and the window covers the whole input) of at most
 // three rows, operands in whole 16-byte vectors: a matrix-vector kernel.

@@ -418,7 +418,7 @@ template <typename T> void launch_gemv(const FwdArgs& a, hipStream_t st) {
 // each.  An fp32 GEMM takes the split count that the model likes best; where
 // that makes a workgroup's share of the taps longer than a piece, the
 // workgroup sums it piece by piece (F32_PIECE).
-FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs) {
+FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs, long max_splits) {
   const int lbk = RB / (int)dt_size(dt);
   const int nkt = (int)((Kg + lbk - 1) / lbk);
   if (dt != BF16) segs = std::max(segs, (nkt + F32_PIECE - 1) / F32_PIECE);
@@ -453,6 +453,7 @@ FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs) {
       if (want > 1 && nkt < 3 * want) break;
       per[ns] = (nkt + want - 1) / want;
       splits[ns] = (nkt + per[ns] - 1) / per[ns];  // every split has a K-tile
+      if (want > 1 && splits[ns] > max_splits) break;
       ++ns;
     }
   }

@@ -27,7 +27,6 @@
 // consecutive rows hit distinct banks.  Two LDS stages: global loads of tile
 // k+1 are in flight while tile k is multiplied.
 #include <algorithm>
-#include <climits>
 
 #include "conv_common.h"
 
@@ -1729,8 +1728,8 @@ template <typename T> int load_mode(long len, const void* p) {
 
 template <typename T>
 hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, const float* bias, void* y,
-                             int relu, int bwd, double flops, float* partial, const void* mask, hipStream_t st,
-                             bool wt = false) {
+                             int relu, int bwd, double flops, float* partial, size_t partial_bytes,
+                             const void* mask, hipStream_t st, bool wt = false) {
   FwdArgs a;
   a.x = x; a.w = w; a.bias = bias; a.y = y; a.mask = mask;
   a.tap_major = 0;
@@ -1761,7 +1760,8 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
   if (vec16 && fwd_gemv_ok(s)) return launch_conv_fwd_gemv(sizeof(T) == 2 ? BF16 : F32, a, bwd, flops, st);
   const bool large = vec16 && sizeof(T) == 2 && use_large_fwd(a.M, a.Nn, a.Kg) && !tuning_env("SINGA_FWD_TILE");
   const int segs = fwd_splits_for(a.M, a.Nn, a.Kg, BK);
-  const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, sizeof(T) == 2 ? BF16 : F32, segs)
+  const long max_splits = partial ? (long)(partial_bytes / ((size_t)a.M * a.Nn * sizeof(float))) : 1;
+  const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, sizeof(T) == 2 ? BF16 : F32, segs, max_splits)
                                            : FwdTilePlan{0, 1, 1};
   const int splits = vec16 ? plan.splits : segs;
   a.partial = splits > 1 ? partial : nullptr;
@@ -2058,36 +2058,43 @@ hipError_t conv_wgrad_dispatch(const ConvShape& s, const void* x, const void* dy
 }  // namespace
 
 hipError_t launch_conv_fwd(int dt, const ConvShape& s, const void* x, const void* w, const float* bias, void* y,
-                           int relu, int bwd, double flops, float* partial, const void* mask, hipStream_t st) {
-  if (dt == BF16) return conv_fwd_dispatch<bf16_t>(s, x, w, bias, y, relu, bwd, flops, partial, mask, st);
-  return conv_fwd_dispatch<float>(s, x, w, bias, y, relu, bwd, flops, partial, mask, st);
+                           int relu, int bwd, double flops, float* partial, size_t partial_bytes, const void* mask,
+                           hipStream_t st) {
+  if (dt == BF16)
+    return conv_fwd_dispatch<bf16_t>(s, x, w, bias, y, relu, bwd, flops, partial, partial_bytes, mask, st);
+  return conv_fwd_dispatch<float>(s, x, w, bias, y, relu, bwd, flops, partial, partial_bytes, mask, st);
 }
 
 hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const void* wt, void* y, int bwd,
-                              double flops, float* partial, const void* mask, hipStream_t st) {
+                              double flops, float* partial, size_t partial_bytes, const void* mask, hipStream_t st) {
   if (dt != BF16 || s.R != 1 || s.S != 1 || s.K % 8 != 0 || (uintptr_t)wt % 16 != 0 ||
       (size_t)s.C * s.K * 2 > 0x7fffffffu)
     return hipErrorNotSupported;
-  return conv_fwd_dispatch<bf16_t>(s, x, wt, nullptr, y, 0, bwd, flops, partial, mask, st, true);
+  return conv_fwd_dispatch<bf16_t>(s, x, wt, nullptr, y, 0, bwd, flops, partial, partial_bytes, mask, st, true);
 }
 
-size_t fwd_partial_bytes(const ConvShape& s, int dt) {
+size_t fwd_partial_bytes(const ConvShape& s, int dt, bool least) {
   const long M = (long)s.N * s.P * s.Q, Nn = s.K, Kg = (long)s.R * s.S * s.C;
   // either kernel may run (the tile kernel also needs aligned pointers)
   const int segs = fwd_splits_for(M, Nn, Kg, dt == BF16 ? KT<bf16_t>::BK : KT<float>::BK);
-  const int splits = dt == BF16 ? segs : std::max(segs, fwd_tile_plan(M, Nn, Kg, dt, segs).splits);
-  return splits > 1 ? (size_t)splits * M * Nn * sizeof(float) : 0;
+  const size_t one = (size_t)M * Nn * sizeof(float);
+  int splits = segs;
+  if (!least && dt == F32)
+    splits = std::max(splits, fwd_tile_plan(M, Nn, Kg, dt, segs, std::max((long)segs, (long)(PARTIAL_ROOM / one))).splits);
+  return splits > 1 ? splits * one : 0;
 }
 
-size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least) {
+size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, size_t room) {
   const size_t Ng = (size_t)s.R * s.S * s.C + (bias ? 1 : 0);
   const size_t ldp = (Ng + 63) / 64 * 64;
   // any of the kernels may run (two of them also need aligned pointers)
   int splits = wgrad_splits_for(s, dt, bias, false);
   if (wgrad_large_shape(s, dt)) splits = std::max(splits, wgrad_splits_for(s, dt, bias, true));
-  if (!least && dt == F32 && s.K % 4 == 0 && s.C % 4 == 0)
-    splits = std::max(splits, wgrad_tile_plan(s.K, (long)Ng, (long)s.N * s.P * s.Q, LONG_MAX, 1).splits);
-  return splits > 1 ? (size_t)splits * s.K * ldp * sizeof(float) : 0;
+  const size_t one = s.K * ldp * sizeof(float);
+  if (dt == F32 && s.K % 4 == 0 && s.C % 4 == 0)
+    splits = std::max(splits, wgrad_tile_plan(s.K, (long)Ng, (long)s.N * s.P * s.Q,
+                                              std::max((long)splits, (long)(room / one)), 1).splits);
+  return splits > 1 ? splits * one : 0;
 }
 
 hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
@@ -2113,12 +2120,13 @@ bool wgrad_update_fusable(const ConvShape& s, int dt, bool bias) {
 }
 
 hipError_t launch_conv_wgrad_reduce_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
-                                        float* dw, float* db, const SgdTargets& u, double flops, hipStream_t st) {
+                                        size_t partial_bytes, float* dw, float* db, const SgdTargets& u, double flops,
+                                        hipStream_t st) {
   if (!partial) return hipErrorNotSupported;
-  const size_t pb = wgrad_partial_bytes(s, dt, u.b != nullptr, false);
+  db = u.b ? db : nullptr;
   if (dt == BF16)
-    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, nullptr, flops, st);
-  return conv_wgrad_dispatch<float>(s, x, dy, partial, pb, dw, u.b ? db : nullptr, 0, 0, &u, nullptr, flops, st);
+    return conv_wgrad_dispatch<bf16_t>(s, x, dy, partial, partial_bytes, dw, db, 0, 0, &u, nullptr, flops, st);
+  return conv_wgrad_dispatch<float>(s, x, dy, partial, partial_bytes, dw, db, 0, 0, &u, nullptr, flops, st);
 }
 
 hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* dw, float* db,

@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "singa_mi.h"
 
 namespace singa {
 
@@ -43,14 +44,23 @@ struct ConvShape {
 // a flipped filter copy, bwd != 0): y = act(conv(x, w) + bias).  `flops` is
 // the algorithmic work of the layer pass this launch carries out.  When the
 // output tiles cannot fill the GPU and `partial` (fwd_partial_bytes() of
-// workspace) is given, the taps are split across workgroups and a second
-// kernel adds the fp32 partial tiles in a fixed order.  `mask` (optional, the
+// workspace, given as partial_bytes) has the room, the taps are split across
+// workgroups and a second kernel adds the fp32 partial tiles in a fixed order.  `mask` (optional, the
 // shape of y) zeroes each output whose mask value is <= 0: the backward of a
 // ReLU whose output is `mask`, folded into the store.
 hipError_t launch_conv_fwd(int dt, const ConvShape& s, const void* x, const void* w, const float* bias,
-                           void* y, int relu, int bwd, double flops, float* partial, const void* mask,
-                           hipStream_t st);
-size_t fwd_partial_bytes(const ConvShape& s, int dt);
+                           void* y, int relu, int bwd, double flops, float* partial, size_t partial_bytes,
+                           const void* mask, hipStream_t st);
+// least: the smallest size that works, which is what the split counts of the
+// register-staged kernels take; an fp32 GEMM then makes no more splits.
+size_t fwd_partial_bytes(const ConvShape& s, int dt, bool least);
+
+// What an fp32 GEMM's split count may take for its partial sums beyond that
+// smallest size.  The splits' time model prices the bytes' time and nothing
+// else: unlimited, a forward of 147,456 x 320 x 44,800 asked for 755 MB to
+// gain 5 %.  Over 3,000 drawn layers the limit costs the model's choice 0.03 %
+// (forward) and 0.08 % (filter gradient) on average, 17 % at worst.
+constexpr size_t PARTIAL_ROOM = 64u << 20;
 
 // The same GEMM for a 1x1 geometry (R = S = 1) with the filter given
 // transposed, wt[c][k] (the K filter columns contiguous), as the dense
@@ -58,7 +68,7 @@ size_t fwd_partial_bytes(const ConvShape& s, int dt);
 // bf16 only, K % 8 == 0, 16-byte aligned wt; otherwise returns
 // hipErrorNotSupported and launches nothing.  No bias, no ReLU.
 hipError_t launch_conv_fwd_wt(int dt, const ConvShape& s, const void* x, const void* wt, void* y, int bwd,
-                              double flops, float* partial, const void* mask, hipStream_t st);
+                              double flops, float* partial, size_t partial_bytes, const void* mask, hipStream_t st);
 
 // Where column ((r' Sg + s') Cg + (dh sw + dw) C + c) of a filter-gradient GEMM
 // goes in the caller's filter: element (r, s, c), r = sh r' + dh, s = sw s' +
@@ -77,9 +87,9 @@ struct FilterMap {
 // workspace; NULL when that is 0) and a second kernel adds them in a fixed
 // order.  `flops` is the algorithmic work of the layer pass this launch
 // carries out (s may be a rewritten geometry with zero taps).
-// least: the smallest size that works (an fp32 layer then makes fewer splits
-// than it would like: partial_bytes is what the partial tiles may take).
-size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least);
+// room: what an fp32 layer may take where the register-staged kernel's split
+// count takes less (0: the smallest size that works).
+size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, size_t room);
 // map: dw is laid out or shaped otherwise than the GEMM's (K, g.R, g.S, g.C)
 // result (see FilterMap).  The reduction of the partial tiles writes it there;
 // a gradient in one piece goes to `staging` as the GEMM has it, not
@@ -87,6 +97,11 @@ size_t wgrad_partial_bytes(const ConvShape& s, int dt, bool bias, bool least);
 hipError_t launch_conv_wgrad(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
                              size_t partial_bytes, float* dw, float* db, int acc_dw, int acc_db, const FilterMap* map,
                              float* staging, int* staged, double flops, hipStream_t st);
+
+// Workspace of singa_conv_bwd_filter in the form with or without a bias (the
+// public query answers for both); the call's own checks of shapes and layout.
+int conv_bwd_filter_bytes(int dtype, int layout, const singa_shape4* x, const singa_filter4* w,
+                          const singa_conv_desc* d, bool bias, size_t* bytes);
 
 // Parameters the filter-gradient kernel updates in place once a gradient
 // element is complete (SGD with momentum, one step per element): the fp32
@@ -115,14 +130,15 @@ hipError_t launch_conv_wgrad_sgd(int dt, const ConvShape& s, const void* x, cons
                                  const SgdTargets& u, hipStream_t st);
 
 // The filter gradient with the update applied by its split-K reduction: the
-// GEMM writes partial tiles into `partial` (wgrad_partial_bytes() of
-// workspace) and the fixed-order reduction applies the step to each summed
+// GEMM writes partial tiles into `partial` (partial_bytes, as in
+// launch_conv_wgrad) and the fixed-order reduction applies the step to each summed
 // element (w, v, wb, and b, vb, bb with a bias), storing the gradient in dw
 // (db) too when not NULL.  When the kernel that runs s would use a single
 // split and cannot take the update itself, returns hipErrorNotSupported and
 // launches nothing.
 hipError_t launch_conv_wgrad_reduce_sgd(int dt, const ConvShape& s, const void* x, const void* dy, float* partial,
-                                        float* dw, float* db, const SgdTargets& u, double flops, hipStream_t st);
+                                        size_t partial_bytes, float* dw, float* db, const SgdTargets& u, double flops,
+                                        hipStream_t st);
 
 // Batched 2-D transpose: for b in [0, batch): out(b)[c][r] = in(b)[r][c] with
 // in(b) = in + in_base(b), out(b) = out + out_base(b), where

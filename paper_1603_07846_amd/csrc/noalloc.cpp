@@ -7,6 +7,8 @@
 
 #include <mutex>
 
+#include "internal.h"
+
 namespace {
 
 // One copy per GPU the library runs on, held until the process ends.  In host
@@ -38,15 +40,13 @@ extern "C" int singa_conv_bwd_filter_noalloc(singa_dtype dtype, singa_layout lay
                                              const void* x_ptr, const singa_filter4* w, const singa_conv_desc* d,
                                              const void* dy_ptr, float* dw, float* db, int accumulate,
                                              singa_stream stream) {
-  // the workspace the allocating call would take (with a bias column: never
-  // less than without one); validation of shapes, dtype and layout happens
-  // here and again in the call below, before anything is enqueued
+  // the workspace that the allocating call takes (its partial sums are limited
+  // so that a call that fits the array in any way fits it whole); validation
+  // happens here and again in the call below, before anything is enqueued
   size_t need = 0;
-  int rc = singa_conv_workspace_bytes(SINGA_OP_BWD_FILTER, dtype, layout, x, w, d, &need);
+  int rc = singa::conv_bwd_filter_bytes(dtype, layout, x, w, d, db != nullptr, &need);
   if (rc != SINGA_OK) return rc;
-  // a size past the array's: the call below takes what fits (fewer splits of
-  // the reduction), or returns SINGA_ERR_WORKSPACE when that is too little
-  if (need > (size_t)SINGA_NOALLOC_SCRATCH_BYTES) need = SINGA_NOALLOC_SCRATCH_BYTES;
+  if (need > (size_t)SINGA_NOALLOC_SCRATCH_BYTES) return SINGA_ERR_SCRATCH;
   void* ws = nullptr;
   if (need > 0) {
     int cur = -1;
@@ -59,6 +59,5 @@ extern "C" int singa_conv_bwd_filter_noalloc(singa_dtype dtype, singa_layout lay
     rc = scratch_address(cur, &ws);
     if (rc != SINGA_OK) return rc;
   }
-  rc = singa_conv_bwd_filter(dtype, layout, x, x_ptr, w, d, dy_ptr, dw, db, accumulate, ws, need, stream);
-  return rc == SINGA_ERR_WORKSPACE ? SINGA_ERR_SCRATCH : rc;
+  return singa_conv_bwd_filter(dtype, layout, x, x_ptr, w, d, dy_ptr, dw, db, accumulate, ws, need, stream);
 }

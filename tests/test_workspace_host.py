@@ -74,3 +74,86 @@ def test_the_reported_workspace_is_enough(op, dt, lay):
             if rc == WORKSPACE:
                 refused.append((shape, bias))
     assert not refused, (len(refused), refused[:5])
+
+
+# ------------------------------------------------- what fp32 has to have
+#
+# The least that an fp32 call works with is what the split counts of the
+# register-staged 128 x 128 kernels take, written down here once more.
+
+def _up(v):
+    return (v + 255) // 256 * 256
+
+
+def _cd(a, b):
+    return -(-a // b)
+
+
+def _gemm_least(M, Nn, Kg):
+    tiles, nkt = _cd(M, 128) * _cd(Nn, 128), _cd(Kg, 32)
+    splits = 1 if tiles >= 256 or nkt < 8 else min(_cd(512, tiles), nkt // 4, 16)
+    splits = _cd(nkt, _cd(nkt, splits)) if splits > 1 else 1
+    return _up(4 * splits * M * Nn) if splits > 1 else 0
+
+
+def _gradient_least(M, Ng, T):
+    tiles, nkt = _cd(M, 128) * _cd(Ng, 128), _cd(T, 32)
+    splits = min(max(min(_cd(1024, tiles), nkt // 8), 1), 256)
+    splits = _cd(nkt, _cd(nkt, splits))
+    return _up(4 * splits * M * _cd(Ng, 64) * 64) if splits > 1 else 0
+
+
+def least(op, shape, bias):
+    """Stride 1, NHWC, channels and filters in vectors of four."""
+    N, H, W, C, K, R, pad, _ = shape
+    Po, Qo, filt = H + 2 * pad - R + 1, W + 2 * pad - R + 1, 4 * K * R * R * C
+    if op == singa.OP_FWD:
+        return _gemm_least(N * Po * Qo, K, R * R * C)
+    if op == singa.OP_BWD_DATA:
+        dense = Po == Qo == 1 and pad == 0
+        M, Nn, Kg = (N, R * R * C, K) if dense else (N * H * W, C, R * R * K)
+        return _up(filt) + _gemm_least(M, Nn, Kg)
+    g = _gradient_least(K, R * R * C + bias, N * Po * Qo)
+    return g if op == singa.OP_BWD_FILTER else _up(filt) + (_up(4 * K) if bias else 0) + g
+
+
+PLAIN = [s for s in SHAPES if s[7] == 1 and s[3] % 4 == 0 and s[4] % 4 == 0]
+PLAIN += [(256, 24, 24, 1792, 320, 5, 2, 1), (128, 13, 13, 1024, 1024, 1, 0, 1), (32, 27, 27, 1024, 1024, 1, 0, 1),
+          (2, 19, 19, 96, 144, 5, 0, 1), (250, 32, 32, 8, 32, 5, 2, 1)]
+
+
+@pytest.mark.parametrize("op", OPS)
+def test_f32_works_with_the_least_and_asks_for_little_more(op):
+    more = 0
+    for shape in PLAIN:
+        call = Call(singa.F32, singa.NHWC, shape)
+        need = [least(OPS[op], shape, bias) for bias in (False, True)]
+        for bias in (False, True):
+            assert call.status(OPS[op], bias, need[bias]) == HIP, (shape, bias)
+            if need[bias] > 0:
+                assert call.status(OPS[op], bias, need[bias] - 1) == WORKSPACE, (shape, bias)
+        grown = call.reported(OPS[op]) - max(need)
+        assert 0 <= grown <= 64 << 20, (shape, grown)
+        more += grown > 0
+    assert more > 0  # the range holds calls that ask for more
+
+
+def test_f32_gradient_in_the_fixed_array():
+    """The allocation-free call takes the whole of what the call with a
+    workspace takes, or is refused where even the least does not fit."""
+    lib = singa.lib()
+
+    def noalloc(call, bias):
+        return lib.singa_conv_bwd_filter_noalloc(call.dt, call.lay, call.x, P, call.w, call.d, P, P,
+                                                 P if bias else None, 0, None)
+    big = [(n, h, h, c, k, r, r // 2, 1) for n, h, c, k, r in
+           itertools.product((8, 32, 64, 128), (13, 27), (128, 512, 1024), (64, 384, 1024), (1, 3, 5))]
+    for shape in PLAIN + big:
+        call = Call(singa.F32, singa.NHWC, shape)
+        for bias in (False, True):
+            assert least(singa.OP_BWD_FILTER, shape, bias) <= singa.NOALLOC_SCRATCH_BYTES
+            assert noalloc(call, bias) == HIP, (shape, bias)
+        assert call.reported(singa.OP_BWD_FILTER) <= singa.NOALLOC_SCRATCH_BYTES
+    # permuted activations alone pass the array's size
+    for bias in (False, True):
+        assert noalloc(Call(singa.F32, singa.NCHW, (256, 55, 55, 64, 64, 3, 1, 1)), bias) == -7
