@@ -305,8 +305,9 @@ struct FwdTilePlan {
 FwdTilePlan fwd_tile_plan(long M, long Nn, long Kg, int dt, int segs, long max_splits);
 hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd, double flops, hipStream_t st);
 // A dense layer (P = Q = 1 and the window covers the whole input) of at most
-// three rows, operands in whole 16-byte vectors: a matrix-vector kernel.
-bool fwd_gemv_ok(const ConvShape& s);
+// three rows and not too short a reduction, operands in whole 16-byte vectors:
+// a matrix-vector kernel.
+bool fwd_gemv_ok(const ConvShape& s, int dt);
 hipError_t launch_conv_fwd_gemv(int dt, const FwdArgs& a, int bwd, double flops, hipStream_t st);
 
 namespace {

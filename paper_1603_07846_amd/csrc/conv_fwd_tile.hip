@@ -316,7 +316,10 @@ template <typename T> void launch_tile_id(const FwdArgs& a, const FwdTilePlan& p
 // hundred columns make enough loads; a lane adds its products in fp32, the
 // wave's lanes are added by a butterfly and the waves in order.  Against the
 // tile kernel with split taps and its reduction: one row, 4096 x 4096 bf16
-// 11.9 -> 7.4 us (4.5 TB/s).
+// 11.9 -> 7.4 us (4.5 TB/s).  At four rows the bf16 tiles are as fast on long
+// reductions (4096 x 4096: 9.4 us, here 9.3) and far ahead on short ones (512
+// taps, 9216 columns: 6.7 against 16.3); in fp32 long ones would still gain
+// (4096 x 4096: 20.2 against 15.1).
 constexpr int GEMV_COLS = 4, GEMV_ROWS = 3;
 
 template <typename T> __device__ __forceinline__ void unpack_vec(const uint4& u, float* f);
@@ -505,8 +508,19 @@ hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd
   return hipGetLastError();
 }
 
-bool fwd_gemv_ok(const ConvShape& s) {
-  return s.N <= GEMV_ROWS && s.P == 1 && s.Q == 1 && s.ph == 0 && s.pw == 0 && s.R == s.H && s.S == s.W;
+// Short reductions leave most of a workgroup's lanes idle, and thousands of
+// workgroups then cost more than the tiles' single round: a column takes this
+// many bytes at least, by rows and columns.  The line is where the tile
+// kernel, timed beside this one on 8 - 9216 taps by 12 - 9216 columns, stops
+// being faster (three rows, bf16, 4096 columns: 256 taps 5.0 us on tiles, 6.1
+// here; 512 taps 6.6 and 6.1.  9216 columns: 16 taps 4.1 and 10.3, 4096 taps
+// 19.6 and 15.4; fp32 4.4 and 10.8, 512 taps 11.0 and 10.3).
+bool fwd_gemv_ok(const ConvShape& s, int dt) {
+  if (s.N > GEMV_ROWS || s.P != 1 || s.Q != 1 || s.ph != 0 || s.pw != 0 || s.R != s.H || s.S != s.W) return false;
+  static constexpr int kLeast[2][GEMV_ROWS][4] = {{{0, 0, 0, 256}, {0, 0, 256, 1024}, {256, 256, 384, 2048}},
+                                                  {{0, 0, 0, 1024}, {0, 256, 512, 4096}, {192, 512, 1024, 4096}}};
+  const int cols = s.K <= 32 ? 0 : s.K <= 1024 ? 1 : s.K <= 4096 ? 2 : 3;
+  return (long)s.R * s.S * s.C * (long)dt_size(dt) >= kLeast[dt == BF16][s.N - 1][cols];
 }
 
 hipError_t launch_conv_fwd_gemv(int dt, const FwdArgs& a, int bwd, double flops, hipStream_t st) {

@@ -1757,11 +1757,12 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
   const int am = load_mode<T>(s.C, x);
   const int bm = wt ? BT16 : load_mode<T>(a.Kg, w);
   const bool vec16 = am == VEC16 && bm == VEC16;
-  if (vec16 && fwd_gemv_ok(s)) return launch_conv_fwd_gemv(sizeof(T) == 2 ? BF16 : F32, a, bwd, flops, st);
+  constexpr int DT = sizeof(T) == 2 ? BF16 : F32;
+  if (vec16 && fwd_gemv_ok(s, DT)) return launch_conv_fwd_gemv(DT, a, bwd, flops, st);
   const bool large = vec16 && sizeof(T) == 2 && use_large_fwd(a.M, a.Nn, a.Kg) && !tuning_env("SINGA_FWD_TILE");
   const int segs = fwd_splits_for(a.M, a.Nn, a.Kg, BK);
   const long max_splits = partial ? (long)(partial_bytes / ((size_t)a.M * a.Nn * sizeof(float))) : 1;
-  const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, sizeof(T) == 2 ? BF16 : F32, segs, max_splits)
+  const FwdTilePlan plan = vec16 && !large ? fwd_tile_plan(a.M, a.Nn, a.Kg, DT, segs, max_splits)
                                            : FwdTilePlan{0, 1, 1};
   const int splits = vec16 ? plan.splits : segs;
   a.partial = splits > 1 ? partial : nullptr;
@@ -1814,7 +1815,7 @@ hipError_t conv_fwd_dispatch(const ConvShape& s, const void* x, const void* w, c
   }
   hipError_t e;
   if (vec16) {
-    e = launch_conv_fwd_tile(sizeof(T) == 2 ? BF16 : F32, a, plan, bwd, flops, st);
+    e = launch_conv_fwd_tile(DT, a, plan, bwd, flops, st);
   } else {
     if (bwd)
       launch_fwd_variant<T, true>(am, bm, a, grid, flops, st);
