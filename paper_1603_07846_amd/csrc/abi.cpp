@@ -484,10 +484,12 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
   const void* wk = w_ptr;  // KRSC filter
   void* dx = dx_ptr;
   const void* nhwc_mask = layout == SINGA_NHWC ? relu_y : nullptr;  // folded into the producing kernel
+  // a unit-stride layer's flipped copy is made from the KCRS filter itself, a
+  // batch of the transpose per channel (a grid's z extent ends at 65,535)
+  const bool from_kcrs = layout == SINGA_NCHW && bwd_data_gemm(s) && !bwd_data_fc(s) && s.C <= 65535;
   if (layout == SINGA_NCHW) {
     e = launch_nchw_to_nhwc(dtype, dy_ptr, o.dy, s.N, s.K, s.P, s.Q, st);
-    // a unit-stride layer's flipped copy is made from the KCRS filter itself
-    if (e == hipSuccess && (bwd_data_fc(s) || !bwd_data_gemm(s))) e = kcrs_to_krsc(dtype, s, w_ptr, o.w, st);
+    if (e == hipSuccess && !from_kcrs) e = kcrs_to_krsc(dtype, s, w_ptr, o.w, st);
     dy = o.dy;
     wk = o.w;
     dx = o.dx;
@@ -514,7 +516,7 @@ int singa_conv_bwd_data(singa_dtype dtype, singa_layout layout, const singa_shap
         if (bwd_data_fc(s)) {
           const int J = RS * s.C;  // wt[(r,s,c)][k] = w[k][(r,s,c)]
           e = launch_transpose(dtype, wk, o.wt, 1, s.K, J, 0, J, 0, s.K, 0, st);
-        } else if (layout == SINGA_NCHW) {  // wt[c][r'][s'][k] = w[k][c][R-1-r'][S-1-s']
+        } else if (from_kcrs) {  // wt[c][r'][s'][k] = w[k][c][R-1-r'][S-1-s']
           e = launch_transpose(dtype, w_ptr, o.wt, s.C, s.K, RS, RS, (long)s.C * RS, (long)RS * s.K, s.K, 2, st);
         } else {  // wt[c][r'][s'][k] = w[k][R-1-r'][S-1-s'][c]
           e = launch_transpose(dtype, wk, o.wt, RS, s.K, s.C, s.C, (long)RS * s.C, s.K, (long)RS * s.K, 1, st);
