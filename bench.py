@@ -103,7 +103,8 @@ def measured_traffic(kernel):
     """HBM bytes per launch of `kernel` from the committed counter summary
     (profiles/traffic.json: FETCH_SIZE + WRITE_SIZE per dispatch, calibrated
     against a copy of known size), or None when there is none for this kernel
-    or its source file has changed since the counters were taken."""
+    or its source, the headers beside it included, has changed since the
+    counters were taken."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None

@@ -84,8 +84,20 @@ def normalize(name: str) -> str:
 
 
 def sha256_of(path: str) -> str:
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    """SHA-256 over a source file and the headers beside it that it includes,
+    directly or through each other, each once in the order they are met."""
+    digest, seen, todo = hashlib.sha256(), set(), [path]
+    while todo:
+        p = todo.pop(0)
+        if p in seen:
+            continue
+        seen.add(p)
+        with open(p, "rb") as f:
+            text = f.read()
+        digest.update(text)
+        near = [os.path.join(os.path.dirname(p), m.decode()) for m in re.findall(rb'^\s*#include "([^"]+)"', text, re.M)]
+        todo += [h for h in near if os.path.exists(h)]
+    return digest.hexdigest()
 
 
 def _counter_rows(path: str, counter: str):

@@ -79,6 +79,26 @@ def test_traffic_dropped_when_the_source_changed(tmp_path, monkeypatch):
     assert bench.measured_traffic("k<1>") is None
 
 
+def test_traffic_dropped_when_a_header_changed(tmp_path, monkeypatch):
+    """Device code of the kernel lives in the headers beside it too."""
+    src, head, deep = tmp_path / "k.hip", tmp_path / "a.h", tmp_path / "b.h"
+    src.write_text('#include <cstdio>\n#include "a.h"\n#include "elsewhere.h"\nkernel\n')
+    head.write_text('#include "b.h"\n#include "a.h"\nloads\n')
+    deep.write_text("waits\n")
+    os.makedirs(tmp_path / "profiles")
+    rec = {"kernel": "k<1>", "source": "k.hip", "source_sha256": profiling.sha256_of(str(src)),
+           "bytes_per_launch": 1234.4}
+    (tmp_path / "profiles" / "traffic.json").write_text(json.dumps(rec))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_traffic("k<1>") == 1234
+    for f in (head, deep):
+        text = f.read_text()
+        f.write_text(text + "other\n")
+        assert bench.measured_traffic("k<1>") is None
+        f.write_text(text)
+        assert bench.measured_traffic("k<1>") == 1234
+
+
 def test_kernel_names_normalized():
     n = profiling.normalize
     assert n("void singa::(anonymous namespace)::conv_wgrad_large_kernel<true, false>"
