@@ -510,14 +510,18 @@ hipError_t launch_conv_fwd_tile(int dt, FwdArgs a, const FwdTilePlan& p, int bwd
 
 // Short reductions leave most of a workgroup's lanes idle, and thousands of
 // workgroups then cost more than the tiles' single round: a column takes this
-// many bytes at least, by rows and columns.  The line is where the tile
-// kernel, timed beside this one on 8 - 9216 taps by 12 - 9216 columns, stops
-// being faster (three rows, bf16, 4096 columns: 256 taps 5.0 us on tiles, 6.1
+// many bytes at least, by rows and columns.  In bf16 the line is where the
+// tile kernel, timed beside this one on 8 - 9216 taps by 12 - 9216 columns,
+// stops being faster (three rows, 4096 columns: 256 taps 5.0 us on tiles, 6.1
 // here; 512 taps 6.6 and 6.1.  9216 columns: 16 taps 4.1 and 10.3, 4096 taps
-// 19.6 and 15.4; fp32 4.4 and 10.8, 512 taps 11.0 and 10.3).
+// 19.6 and 15.4).  fp32 stays here longer, since this kernel's many short sums
+// are nearer to 64 bits than a tile's one (64 taps 6.7e-8 and 1.5e-7): up to
+// where the 128 x 128 kernel that had these layers first was faster (three
+// rows, 9216 columns: 64 taps 8.3 us, 11.0 here and 5.3 on tiles; 128 taps
+// 12.7 and 10.9).
 bool fwd_gemv_ok(const ConvShape& s, int dt) {
   if (s.N > GEMV_ROWS || s.P != 1 || s.Q != 1 || s.ph != 0 || s.pw != 0 || s.R != s.H || s.S != s.W) return false;
-  static constexpr int kLeast[2][GEMV_ROWS][4] = {{{0, 0, 0, 256}, {0, 0, 256, 1024}, {256, 256, 384, 2048}},
+  static constexpr int kLeast[2][GEMV_ROWS][4] = {{{0, 0, 0, 0}, {0, 0, 0, 256}, {0, 0, 0, 512}},
                                                   {{0, 0, 0, 1024}, {0, 256, 512, 4096}, {192, 512, 1024, 4096}}};
   const int cols = s.K <= 32 ? 0 : s.K <= 1024 ? 1 : s.K <= 4096 ? 2 : 3;
   return (long)s.R * s.S * s.C * (long)dt_size(dt) >= kLeast[dt == BF16][s.N - 1][cols];
