@@ -32,7 +32,9 @@
  *     element size; the ReLU and update calls need 16-byte alignment.  The
  *     convolution and pooling kernels take 16-byte vector paths when the
  *     pointers are 16-byte aligned and the channel count allows, and
- *     element-wise paths otherwise (same results).
+ *     element-wise paths otherwise (the same products; an fp32 convolution,
+ *     or a bf16 dense layer of one to three rows, may add them in another
+ *     order).
  *   - Calls are asynchronous on `stream` (a hipStream_t; NULL is the legacy
  *     null stream).  The library never synchronizes.  A kernel fault shows
  *     up at the caller's next synchronization.

@@ -456,6 +456,8 @@ hipError_t launch_space_to_depth(int dt, const ConvShape& s, const ConvShape& g,
   const int total = g.N * g.H * g.W * J;
   TraceScope ts("space_to_depth_kernel", st,
                 ((double)s.N * s.H * s.W * s.C + (double)g.N * g.H * g.W * g.C) * dt_size(dt), WORK_BYTE);
+  // whole words only (3 channels at stride 4, in practice): the run's length is
+  // the kernel's word count; other factors keep the gather
   if (dt == BF16 && s.sw * s.C == 12 && (uintptr_t)x % 4 == 0) {
     const int runs = g.N * g.H * g.W * s.sh;
     hipLaunchKernelGGL(space_to_depth_run_kernel, dim3(grid_for(runs)), dim3(256), 0, st, (const bf16_t*)x,

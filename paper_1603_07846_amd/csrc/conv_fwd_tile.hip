@@ -280,7 +280,8 @@ __global__ __launch_bounds__(64 * TileDef<ID>::NW, kWorkgroupsPerCu<ID>) void co
   }
 }
 
-// "conv_fwd_kernel<dtype,tile rows x tile columns,bwd>"
+// "conv_fwd_kernel<dtype,tile rows x tile columns,bwd>"; the profiler's
+// conv_fwd_tile_kernel<dtype, tile, several pieces>, tile as in kTileRows
 #define TILE_NAME(T, M, N, B) "conv_fwd_kernel<" T "," #M "x" #N "," #B ">"
 #define TILE_NAMES(T, B) {TILE_NAME(T, 256, 128, B), TILE_NAME(T, 192, 128, B), TILE_NAME(T, 256, 64, B), TILE_NAME(T, 128, 128, B), TILE_NAME(T, 64, 128, B), TILE_NAME(T, 128, 64, B), TILE_NAME(T, 64, 64, B), TILE_NAME(T, 128, 32, B), TILE_NAME(T, 32, 128, B)}
 constexpr const char* kTileNames[2][2][TILES] = {{TILE_NAMES("f32", 0), TILE_NAMES("f32", 1)},

@@ -1926,7 +1926,13 @@ int wgrad_splits_for(const ConvShape& s, int dt, bool bias, bool large) {
     // 2.5 % faster than 640 (1280 for conv2) and 512, which fill the chip
     // or spill into a second round.  A layer of at most 4 output tiles takes
     // 640 (AlexNet's conv1, whose long reduction runs last, with nothing
-    // beside it: 8 us per step faster).  SINGA_WGRAD_TARGET overrides both.
+    // beside it: 8 us per step faster).  With nothing beside it 448 is no
+    // worse: a target of 512 comes to a few workgroups more than the slots,
+    // whose second round costs more than the empty slots (64 x 27 x 27 x 96,
+    // 256 filters of 5 x 5, with the reduction: 384 81.8 us, 448 78.4, 512
+    // 102.8, 640 91.4; 100 x 13 x 13 x 384, 384 of 3 x 3: 75.2, 71.5, 90.8,
+    // 83.1; 12 layers, 448 at most 4 % behind the best).
+    // SINGA_WGRAD_TARGET overrides both.
     static const long forced = [] {
       const char* e = tuning_env("SINGA_WGRAD_TARGET");
       const long v = e ? atol(e) : 0;

@@ -3,7 +3,7 @@
 // buffer loads into LDS.
 //
 // Serves fp32 layers whose filter and tap chunks are whole 16-byte vectors
-// (K % 4 == 0, C % 4 == 0).  v_mfma_f32_32x32x2_f32 takes 64 cycles for 4,096
+// (K % 4 == 0, C % 4 == 0).  v_mfma_f32_32x32x2_f32 takes 64 cycles for 2,048
 // multiply-adds, so a full tile is bound by the matrix cores and rows of
 // padding cost in proportion: a layer of 32 filters on the 128-row tile spends
 // three quarters of its time on zeros.  Small layers are bound by the few
@@ -206,7 +206,8 @@ __global__ __launch_bounds__(NT, 2) void conv_wgrad_tile_kernel(WgradArgs a) {
   }
 }
 
-// "conv_wgrad_kernel<f32,tile rows x tile columns,image fastest>"
+// "conv_wgrad_kernel<f32,tile rows x tile columns,image fastest>"; the profiler's
+// conv_wgrad_tile_kernel<tile, image fastest, several pieces>, tile as in kWRows
 constexpr const char* kWNames[WTILES][2] = {
     {"conv_wgrad_kernel<f32,128x128,0>", "conv_wgrad_kernel<f32,128x128,1>"},
     {"conv_wgrad_kernel<f32,64x128,0>", "conv_wgrad_kernel<f32,64x128,1>"},
