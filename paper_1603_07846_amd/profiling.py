@@ -6,6 +6,9 @@ Subcommands (run from the repository root):
       A plain device-to-device copy of N MiB, five times: the known-size
       kernel whose FETCH_SIZE / WRITE_SIZE counters calibrate the HBM byte
       counts of the library's kernels.
+  case NAME [NAME ...] [--passes N]
+      N passes of listed performance cases (perf/cases.py), one after another:
+      a short program for kernel traces and counter passes.
   stats KERNEL_STATS_CSV --title T --command C [--trace KERNEL_TRACE_CSV]
       Markdown table of a `rocprofv3 --kernel-trace --stats` summary (with the
       per-kernel median launch time when the same run's trace is given).
@@ -222,6 +225,19 @@ def cmd_libgemm(args):
               flush=True)
 
 
+def cmd_case(args):
+    import torch
+
+    sys.path.insert(0, os.getcwd())
+    from perf import cases
+    listed = {c["name"]: c for c in cases.listed()}
+    for name in args.names:
+        state = cases.prepare(listed[name], 1)
+        for _ in range(args.passes):
+            cases.run(state)
+        torch.cuda.synchronize()
+
+
 def _copy_factor(path, counter, nbytes):
     rows = _counter_rows(path, counter)
     vals = [v * 1024.0 for _, v in rows.values() if v > 0]
@@ -395,6 +411,9 @@ def main(argv=None):
     sub = ap.add_subparsers(dest="cmd", required=True)
     c = sub.add_parser("copy")
     c.add_argument("--mib", type=int, default=1024)
+    w = sub.add_parser("case")
+    w.add_argument("names", nargs="+")
+    w.add_argument("--passes", type=int, default=3)
     s = sub.add_parser("stats")
     s.add_argument("csv")
     s.add_argument("--title", required=True)
@@ -418,7 +437,7 @@ def main(argv=None):
     g = sub.add_parser("libgemm")
     g.add_argument("--reps", type=int, default=20)
     args = ap.parse_args(argv)
-    {"copy": cmd_copy, "stats": cmd_stats, "traffic": cmd_traffic, "counters": cmd_counters,
+    {"copy": cmd_copy, "case": cmd_case, "stats": cmd_stats, "traffic": cmd_traffic, "counters": cmd_counters,
      "libgemm": cmd_libgemm, "timeline": cmd_timeline}[args.cmd](args)
 
 
