@@ -115,7 +115,7 @@ int singa_pool_out_shape(const singa_shape4* x, const singa_pool_desc* d, singa_
 
 /* Workspace bytes that `op` needs for this problem (0 when none), with a bias
  * or without (the form without can need more: a filter gradient of one column
- * less may be cut into more partial sums).  An fp32 call takes up to 64 MiB
+ * less may be cut into more partial sums).  An fp32 call takes up to 128 MiB
  * of this for more partial sums than it has to make; with a workspace that is
  * too small for those it makes fewer (the results then differ in rounding),
  * down to SINGA_ERR_WORKSPACE.  Host-only.

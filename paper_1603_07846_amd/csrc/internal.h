@@ -56,11 +56,15 @@ hipError_t launch_conv_fwd(int dt, const ConvShape& s, const void* x, const void
 size_t fwd_partial_bytes(const ConvShape& s, int dt, bool least);
 
 // What an fp32 GEMM's split count may take for its partial sums beyond that
-// smallest size.  The splits' time model prices the bytes' time and nothing
-// else: unlimited, a forward of 147,456 x 320 x 44,800 asked for 755 MB to
-// gain 5 %.  Over 3,000 drawn layers the limit costs the model's choice 0.03 %
-// (forward) and 0.08 % (filter gradient) on average, 17 % at worst.
-constexpr size_t PARTIAL_ROOM = 64u << 20;
+// smallest size: as much as the fixed scratch array holds.  The splits' time
+// model prices the bytes' time and nothing else: unlimited, a forward of
+// 147,456 x 320 x 44,800 asked for 755 MB to gain 6 % (34.6 -> 32.5 ms; the
+// 128 x 128 kernel 39.0).  Of 3,000 drawn layers the limit changes the choice
+// for 6, by at most 2 % of the model's time; the most seen is 8 % (gradient of
+// 128 x 13 x 13 x 512, 256 filters of 3 x 3: 457 -> 495 us, 536 with the 128 x
+// 128 kernel).  At 64 MiB one layer was slower than with that kernel (gradient
+// of 128 x 13 x 13 x 1024, 1024 filters of 1 x 1: 526 us, 510; now 485).
+constexpr size_t PARTIAL_ROOM = 128u << 20;
 
 // The same GEMM for a 1x1 geometry (R = S = 1) with the filter given
 // transposed, wt[c][k] (the K filter columns contiguous), as the dense
